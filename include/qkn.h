@@ -46,7 +46,9 @@
  *     and d_local are multiples of 8 (bf16) or 16 (fp8), with tp <= 64: rows
  *     held in registers up to d_local = 4096, wider rows with gamma in LDS up
  *     to 16384 columns over both tensors together; otherwise a general path
- *     gives the same bits, more slowly. Alignment is never an error.
+ *     gives the same bits, more slowly: rows of any width and alignment up to
+ *     4096 columns in registers too, the rest staged through LDS. Alignment is
+ *     never an error.
  */
 #ifndef QKN_H
 #define QKN_H
@@ -325,8 +327,10 @@ int qkn_last_launch(qkn_launch_info* info);
  *   "token_blocks"   1 = each wavefront takes a contiguous range of tokens,
  *                    0 = tokens strided by the wavefront count (default);
  *   "waves_per_block" 1..4, 0 = automatic (register path: 1 for bf16,
- *                    4 for fp8; wide path: always 4);
- *   "force_generic"  1 = always take the general path (same results);
+ *                    4 for fp8 and for rows of any alignment; wide path:
+ *                    always 4);
+ *   "force_generic"  1 = always take the general path's staged kernel (same
+ *                    results);
  *   "proj_tile"      qkn_proj_partial's kernel: 0 = automatic (split k for
  *                    decode-sized launches, else kernel 1), 1 = direct-to-
  *                    LDS two-stage kernel on 16 x 16 x 32 MFMAs, never split,

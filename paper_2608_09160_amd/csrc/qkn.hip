@@ -49,6 +49,8 @@ struct FormatInfo {
 constexpr FormatInfo kFormat[2] = {{2, 8, 8, {16, 32}, "", 24 * 1024, 1},
                                    {1, 16, 4, {8, 16}, "_fp8", 28 * 1024, 4}};
 
+constexpr int kAnyWavesPerBlock = 4;  // rows of any alignment: workgroup size in wavefronts
+
 constexpr int kMaxWideLdsBytes = 64 * 1024;  // gamma of both tensors staged by the wide path
 
 // Chunks per lane are rounded up to 1, 2, 4 or 8; unused chunks are masked.
@@ -309,19 +311,22 @@ int launch(const HSeg* segs, int nseg, int tp, int rank, int64_t T, float eps, i
                              (static_cast<__int128>(1) << 31);
   bool fast = buffer_ok;
   bool wide = buffer_ok && !waits;
+  bool any = buffer_ok && !waits;
   int idx[2] = {0, 0};
   int max_chunks = 0;
   int64_t gamma_floats = 0;
   for (int i = 0; i < nseg; ++i) {
     kp.seg[i] = to_dev(segs[i], mode, fi);
     const int per_lane = (kp.seg[i].nchunks + kWave - 1) / kWave;
+    if (per_lane <= fi.reg_max) idx[i] = kNIdx[per_lane];
     if (!kp.seg[i].vec || per_lane > fi.reg_max) fast = false;
-    else idx[i] = kNIdx[per_lane];
+    // rows of at least one 16-byte vector that the registers hold
+    if (kp.seg[i].d < fi.per || per_lane > fi.reg_max) any = false;
     if (!kp.seg[i].vec || per_lane > fi.wide_n0[1]) wide = false;
     if (kp.seg[i].nchunks > max_chunks) max_chunks = kp.seg[i].nchunks;
     gamma_floats += kp.seg[i].d;
   }
-  if (fast) wide = false;
+  if (fast) wide = any = false;
   if (mode != kPartial && gamma_floats * 4 > kMaxWideLdsBytes) wide = false;
   int wide_i0 = 0, wide_i1 = 0;
   if (wide) {
@@ -376,6 +381,17 @@ int launch(const HSeg* segs, int nseg, int tp, int rank, int64_t T, float eps, i
       else fn = reinterpret_cast<const void*>(kPartialTable8[idx[0]]);
     }
     name = rows_name(fmt, mode, sched, idx[0], i1);
+  } else if (any) {
+    // Widths, strides or addresses that 16-byte vectors do not divide, up to the
+    // register path's widths: rows in registers as there, fetched at element
+    // alignment (7999 tokens of 1100 + 100 bf16 columns: 10.3 us, 3.7 TB/s,
+    // against 40.1 us in the staged general kernel). The staged kernel keeps
+    // what fits no register kernel: rows under 16 bytes or over 4096 columns,
+    // more than 64 ranks, slot arrays beyond 32-bit offsets.
+    if (mode == kFused) fn = reinterpret_cast<const void*>(kAnyFusedTable[fmt][idx[0]][i1]);
+    else if (mode == kApply) fn = reinterpret_cast<const void*>(kAnyApplyTable[fmt][idx[0]]);
+    else fn = reinterpret_cast<const void*>(kAnyPartialTable[fmt][idx[0]]);
+    name = kGenericName[fmt][mode];
   } else {
     fn = reinterpret_cast<const void*>(kGenericTable[fmt][mode]);
     name = kGenericName[fmt][mode];
@@ -394,12 +410,15 @@ int launch(const HSeg* segs, int nseg, int tp, int rank, int64_t T, float eps, i
   int rc = query_device(&dev, &cus);
   if (rc != QKN_OK) return rc;
   int wpb = 1;
-  if (fast && !waits) {
+  if ((fast || any) && !waits) {
     // multi-wave workgroups only when the tokens fill every CU several times
-    // over; short launches (decode) spread one-wave workgroups over more CUs
+    // over; short launches (decode) spread one-wave workgroups over more CUs.
+    // Rows of any alignment: four-wave ones in bf16 too (1100 + 100 columns,
+    // 7999 tokens 10.3 against 11.0 us; 2200 + 1001, 8192 tokens 19.4 against 21.0)
+    const int many = any ? kAnyWavesPerBlock : fi.waves_per_block;
     if (g_opt_waves_per_block > 0) wpb = static_cast<int>(g_opt_waves_per_block);
-    else if (T >= static_cast<int64_t>(cus) * fi.waves_per_block * kMinWavesPerCu)
-      wpb = fi.waves_per_block;
+    else if (T >= static_cast<int64_t>(cus) * many * kMinWavesPerCu)
+      wpb = many;
   }
   if (wide) wpb = 4;  // four wavefronts share the gamma staged in LDS
   const int block = wpb * kWave;
@@ -409,7 +428,7 @@ int launch(const HSeg* segs, int nseg, int tp, int rank, int64_t T, float eps, i
   // Persistent grid: enough wavefronts per CU to keep about fi.inflight_bytes
   // of rows requested per CU, at least kMinWavesPerCu, at most what fits.
   int64_t waves_per_cu = static_cast<int64_t>(bpc) * wpb;
-  if (fast || wide) {  // waiting launches too: fewer waves only loosen the co-residency bound below
+  if (fast || any || wide) {  // waiting launches too: fewer waves only loosen the co-residency bound below
     int64_t token_bytes = 0;
     for (int i = 0; i < nseg; ++i) token_bytes += fi.esz * static_cast<int64_t>(kp.seg[i].d);
     int64_t want = (fi.inflight_bytes + token_bytes - 1) / token_bytes;
@@ -439,7 +458,7 @@ int launch(const HSeg* segs, int nseg, int tp, int rank, int64_t T, float eps, i
     waves = per_rank * group;
   } else if (waves > T) {
     waves = T;
-  } else if (fast && g_opt_balance) {
+  } else if ((fast || any) && g_opt_balance) {
     // equal shares: k tokens per wavefront for every wavefront (but the last),
     // so that none runs an extra token while the others are done
     const int64_t k = (T + waves - 1) / waves;
@@ -447,10 +466,10 @@ int launch(const HSeg* segs, int nseg, int tp, int rank, int64_t T, float eps, i
   }
   int64_t grid = (waves + wpb - 1) / wpb;
   if (grid > 0x7fffffff) grid = 0x7fffffff;
-  if (fast && g_opt_token_blocks) kp.tok_chunk = (T + grid * wpb - 1) / (grid * wpb);
+  if ((fast || any) && g_opt_token_blocks) kp.tok_chunk = (T + grid * wpb - 1) / (grid * wpb);
 
   hipError_t err;
-  if (fast || wide) {
+  if (fast || any || wide) {
     void* args[] = {&kp};
     err = hipLaunchKernel(fn, dim3(static_cast<unsigned>(grid)), dim3(block), args, lds,
                           static_cast<hipStream_t>(stream));

@@ -555,17 +555,190 @@ __device__ __forceinline__ void store_scaled_at(uintptr_t row, uint32_t bytes, i
   }
 }
 
+// Phase C of one chunk: y = round((x * gamma) * inv), gamma from kGammaVecs<F> vectors.
+template <class F>
+__device__ __forceinline__ u32x4 scale_chunk(u32x4 v, const f32x4* g, float inv) {
+  constexpr int kG = kGammaVecs<F>;
+  f32x4 gq[kG];
+#pragma unroll
+  for (int j = 0; j < kG; ++j) gq[j] = g[j];
+  float f[F::kPer];
+  F::unpack(v, f);
+  float o[F::kPer];
+#pragma unroll
+  for (int e = 0; e < F::kPer; ++e) o[e] = (f[e] * gq[e >> 2][e & 3]) * inv;
+  return F::pack(o);
+}
+
+// ---- rows of any width and alignment (qkn_rows with ANY)
+//
+// The same register-resident rows where 16-byte vectors do not divide the row
+// or its address: lane l still takes the 16 bytes of chunk l, l + 64, ...,
+// through 16-byte global accesses at element alignment. A chunk that would run
+// past the row's end (the partial last one, and the empty ones behind it) is
+// fetched as the row's last 16 bytes instead, unconditionally, so that the
+// loads stay branch-free, and shifted into place once it is used; what lies
+// behind the row reads as zero. Rows are at least 16 bytes long.
+// Bound by instruction issue rather than by HBM (38 MB in 10.3 us at 7999
+// tokens of 1100 + 100 bf16 columns; 40.1 us in the staged general kernel,
+// whose lanes take such rows element by element): hence the rounds of chunks
+// that a row does not have are skipped by scalar branches (13.5 -> 11.3 us
+// together with keeping no lane masks over the loop), and x is loaded with the
+// default policy, since neighbouring lanes' and rows' requests meet in a cache
+// line (12.6 against 13.4 us non-temporal).
+
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef uint64_t u64_any __attribute__((aligned(1)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
+typedef const __attribute__((address_space(1))) unsigned char* GlobalIn;
+typedef __attribute__((address_space(1))) unsigned char* GlobalOut;
+template <class V>
+using GlobalInOf = const __attribute__((address_space(1))) V*;
+template <class V>
+using GlobalOutOf = __attribute__((address_space(1))) V*;
+
+// Round i of a row's chunks (one per lane): whether every lane's is whole, whether any exists.
+__device__ __forceinline__ bool whole_any(int i, uint32_t bytes) {
+  return static_cast<uint32_t>(i + 1) * (kWave * 16u) <= bytes;
+}
+__device__ __forceinline__ bool live_any(int i, uint32_t bytes) {
+  return static_cast<uint32_t>(i) * (kWave * 16u) < bytes;
+}
+
+// The row's length, hidden from the compiler once per token: the lane masks
+// that follow from it are then formed where they are used (a few comparisons
+// in one round of chunks) instead of being kept, and spilled, over the loop.
+__device__ __forceinline__ uint32_t bytes_any(uint32_t bytes) {
+  asm volatile("" : "+s"(bytes));
+  return bytes;
+}
+
+template <int N>
+__device__ __forceinline__ void load_row_any(uintptr_t row, uint32_t bytes, int lane, u32x4 (&x)[N]) {
+  const GlobalIn base = reinterpret_cast<GlobalIn>(row);
+  const uint32_t last = bytes - 16u;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (i > 0 && !live_any(i, bytes)) continue;
+    const uint32_t at = static_cast<uint32_t>(i * kWave + lane) * 16u;
+    x[i] = *reinterpret_cast<GlobalInOf<u32x4_any>>(base + (at < last ? at : last));
+  }
+}
+
+// Chunks fetched at the row's end move down to their own columns (zeros behind the row).
+template <int N>
+__device__ __forceinline__ void settle_row_any(uint32_t bytes, int lane, u32x4 (&x)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    // every lane's chunk is whole, or none exists
+    if (whole_any(i, bytes) || !live_any(i, bytes)) continue;
+    const uint32_t at = static_cast<uint32_t>(i * kWave + lane) * 16u;
+    const uint32_t by = at + 16u > bytes ? at + 16u - bytes : 0u;  // bytes fetched ahead of the chunk
+    u32x4 v = x[i];
+    if (by & 8u) v = u32x4{v[2], v[3], 0u, 0u};
+    if (by & 4u) v = u32x4{v[1], v[2], v[3], 0u};
+    u32x4 r;
+    r[0] = __builtin_amdgcn_alignbyte(v[1], v[0], by & 3u);
+    r[1] = __builtin_amdgcn_alignbyte(v[2], v[1], by & 3u);
+    r[2] = __builtin_amdgcn_alignbyte(v[3], v[2], by & 3u);
+    r[3] = __builtin_amdgcn_alignbyte(0u, v[3], by & 3u);
+    x[i] = by < 16u ? r : u32x4{0u, 0u, 0u, 0u};
+  }
+}
+
+// gamma of a lane's chunks, fetched and moved into place the same way (four
+// floats at a time); values behind the row's end are never used.
+template <class F, int N>
+__device__ __forceinline__ void load_gamma_any(const float* w, int d, int lane,
+                                               f32x4 (&g)[N][kGammaVecs<F>]) {
+  constexpr int kG = kGammaVecs<F>;
+  const GlobalInOf<float> base = (GlobalInOf<float>)w;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int j = 0; j < kG; ++j) {
+      const int at = ((i * kWave + lane) * kG + j) * 4;
+      g[i][j] = *reinterpret_cast<GlobalInOf<f32x4_any>>(base + (at < d - 4 ? at : d - 4));
+    }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if ((i + 1) * kWave * F::kPer <= d) continue;
+#pragma unroll
+    for (int j = 0; j < kG; ++j) {
+      const int at = ((i * kWave + lane) * kG + j) * 4;
+      const int by = at + 4 > d ? at + 4 - d : 0;
+      f32x4 v = g[i][j];
+      if (by & 2) v = f32x4{v[2], v[3], v[3], v[3]};
+      if (by & 1) v = f32x4{v[1], v[2], v[3], v[3]};
+      g[i][j] = v;
+    }
+  }
+}
+
+// Phases A and B's products over the rounds of chunks that exist.
+template <class F, int N>
+__device__ __forceinline__ float row_lane_sumsq_any(uint32_t bytes, const u32x4 (&x)[N]) {
+  float acc = 0.0f;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (i == 0 || live_any(i, bytes)) acc = chunk_sumsq<F>(x[i], acc);
+  return acc;
+}
+
+// Phase C (and Phase B's products): whole chunks as 16-byte stores, the
+// partial last one in halving pieces.
+template <class F, int N>
+__device__ __forceinline__ void store_scaled_any(uintptr_t row, uint32_t bytes, int lane,
+                                                 const u32x4 (&x)[N], const f32x4 (&g)[N][kGammaVecs<F>],
+                                                 float inv) {
+  const GlobalOut base = reinterpret_cast<GlobalOut>(row);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (i > 0 && !live_any(i, bytes)) continue;
+    u32x4 v = scale_chunk<F>(x[i], g[i], inv);
+    uint32_t at = static_cast<uint32_t>(i * kWave + lane) * 16u;
+    if (whole_any(i, bytes) || at + 16u <= bytes) {
+      __builtin_nontemporal_store(v, reinterpret_cast<GlobalOutOf<u32x4_any>>(base + at));
+    } else if (at < bytes) {
+      const uint32_t n = bytes - at;
+      if (n & 8u) {
+        *reinterpret_cast<GlobalOutOf<u64_any>>(base + at) = (static_cast<uint64_t>(v[1]) << 32) | v[0];
+        v = u32x4{v[2], v[3], 0u, 0u};
+        at += 8u;
+      }
+      if (n & 4u) {
+        *reinterpret_cast<GlobalOutOf<u32_any>>(base + at) = v[0];
+        v[0] = v[1];
+        at += 4u;
+      }
+      if (n & 2u) {
+        *reinterpret_cast<GlobalOutOf<u16_any>>(base + at) = static_cast<uint16_t>(v[0]);
+        v[0] >>= 16;
+        at += 2u;
+      }
+      if (sizeof(typename F::Elem) == 1 && (n & 1u)) base[at] = static_cast<unsigned char>(v[0]);
+    }
+  }
+}
+
 // `live` false (a pipelined request past the last token): nothing is fetched.
 // POLL false (wait mode, publish-ahead schedule): the rows only; the first poll
 // of the token's slots is issued later, once the other ranks have had time to
 // publish.
-template <class F, int N0, int N1, int MODE, bool POLL = true>
+template <class F, int N0, int N1, int MODE, bool POLL = true, bool ANY = false>
 __device__ __forceinline__ void fetch_token(const KParams& p, const Cursor& c,
                                             const CursorBytes& nb, int lane, int own_rank,
                                             TokenRegs<N0, (N1 > 0 ? N1 : 1)>& r,
                                             bool live = true) {
-  load_row_at<N0>(c.x[0], nb.row[0], lane, r.x0, live);
-  if constexpr (N1 > 0) load_row_at<N1>(c.x[1], nb.row[1], lane, r.x1, live);
+  if constexpr (ANY) {
+    load_row_any<N0>(c.x[0], nb.row[0], lane, r.x0);
+    if constexpr (N1 > 0) load_row_any<N1>(c.x[1], nb.row[1], lane, r.x1);
+  } else {
+    load_row_at<N0>(c.x[0], nb.row[0], lane, r.x0, live);
+    if constexpr (N1 > 0) load_row_at<N1>(c.x[1], nb.row[1], lane, r.x1, live);
+  }
   r.slots0 = 0.0f;
   r.slots1 = 0.0f;
   if constexpr (MODE == kFused || MODE == kApply) {
@@ -635,16 +808,25 @@ __device__ __forceinline__ void finish_waiting_token(
 }
 
 // Phases A, B and C of the token at cursor `c`, whose rows and slots are in `r`.
-template <class F, int N0, int N1, int MODE>
+template <class F, int N0, int N1, int MODE, bool ANY = false>
 __device__ __forceinline__ void process_token(const KParams& p, const Cursor& c,
                                               const CursorBytes& nb, int lane, int own_rank,
                                               const f32x4 (&g0)[N0][kGammaVecs<F>],
                                               const f32x4 (&g1)[(N1 > 0 ? N1 : 1)][kGammaVecs<F>],
-                                              const TokenRegs<N0, (N1 > 0 ? N1 : 1)>& r,
+                                              TokenRegs<N0, (N1 > 0 ? N1 : 1)>& r,
                                               bool& given_up) {
   constexpr int M1 = N1 > 0 ? N1 : 1;
   const DevSeg& s0 = p.seg[0];
   const DevSeg& s1 = p.seg[1];
+  uint32_t b0 = 0, b1 = 0;  // row lengths (ANY)
+  if constexpr (ANY) {
+    b0 = bytes_any(nb.row[0]);
+    settle_row_any<N0>(b0, lane, r.x0);
+    if constexpr (N1 > 0) {
+      b1 = bytes_any(nb.row[1]);
+      settle_row_any<N1>(b1, lane, r.x1);
+    }
+  }
   if constexpr (MODE == kFusedWait) {
     // publish this rank's statistics before waiting for the others'
     float own0, own1;
@@ -657,8 +839,13 @@ __device__ __forceinline__ void process_token(const KParams& p, const Cursor& c,
   // Phase A: per-lane partial sums (not needed when every slot is given).
   float a0 = 0.0f, a1 = 0.0f;
   if constexpr (MODE != kApply) {
-    a0 = row_lane_sumsq<F, N0>(r.x0);
-    if constexpr (N1 > 0) a1 = row_lane_sumsq<F, N1>(r.x1);
+    if constexpr (ANY) {
+      a0 = row_lane_sumsq_any<F, N0>(b0, r.x0);
+      if constexpr (N1 > 0) a1 = row_lane_sumsq_any<F, N1>(b1, r.x1);
+    } else {
+      a0 = row_lane_sumsq<F, N0>(r.x0);
+      if constexpr (N1 > 0) a1 = row_lane_sumsq<F, N1>(r.x1);
+    }
   }
 
   if constexpr (MODE == kPartial) {
@@ -675,10 +862,14 @@ __device__ __forceinline__ void process_token(const KParams& p, const Cursor& c,
     }
 
     // Phase B, compute path: independent of the statistic.
+    // (ANY: the products are formed chunk by chunk in Phase C, which keeps
+    // fewer values over its branches.)
     float z0[N0][F::kPer];
     float z1[M1][F::kPer];
-    times_gamma<F, N0>(r.x0, g0, z0);
-    if constexpr (N1 > 0) times_gamma<F, N1>(r.x1, g1, z1);
+    if constexpr (!ANY) {
+      times_gamma<F, N0>(r.x0, g0, z0);
+      if constexpr (N1 > 0) times_gamma<F, N1>(r.x1, g1, z1);
+    }
 
     // Phase B, reduction path.
     const float slots0 = r.slots0, slots1 = r.slots1;
@@ -691,8 +882,13 @@ __device__ __forceinline__ void process_token(const KParams& p, const Cursor& c,
     }
 
     // Phase C.
-    store_scaled_at<F, N0>(c.y[0], nb.row[0], lane, z0, inv0);
-    if constexpr (N1 > 0) store_scaled_at<F, N1>(c.y[1], nb.row[1], lane, z1, inv1);
+    if constexpr (ANY) {
+      store_scaled_any<F, N0>(c.y[0], b0, lane, r.x0, g0, inv0);
+      if constexpr (N1 > 0) store_scaled_any<F, N1>(c.y[1], b1, lane, r.x1, g1, inv1);
+    } else {
+      store_scaled_at<F, N0>(c.y[0], nb.row[0], lane, z0, inv0);
+      if constexpr (N1 > 0) store_scaled_at<F, N1>(c.y[1], nb.row[1], lane, z1, inv1);
+    }
     if constexpr (MODE == kFused) {
       st4f_lane0(own0, rsrc_of(c.own[0], nb.own[0]), lane);
       if constexpr (N1 > 0) st4f_lane0(own1, rsrc_of(c.own[1], nb.own[1]), lane);
@@ -703,7 +899,7 @@ __device__ __forceinline__ void process_token(const KParams& p, const Cursor& c,
 }
 
 // The cursors of token t and their per-token strides (`step` tokens apart).
-template <class F, int MODE>
+template <class F, int MODE, bool ANY = false>
 __device__ __forceinline__ void make_cursors(const KParams& p, const WaveSlice& ws, int64_t t,
                                              int64_t step, Cursor& c, Cursor& dc,
                                              CursorBytes& nb) {
@@ -717,7 +913,7 @@ __device__ __forceinline__ void make_cursors(const KParams& p, const WaveSlice& 
     dc.x[i] = step * s.ldx * kEsz;
     c.y[i] = reinterpret_cast<uintptr_t>(s.y) + (t * s.ldy + col) * kEsz;
     dc.y[i] = step * s.ldy * kEsz;
-    nb.row[i] = used ? static_cast<uint32_t>(s.nchunks) * 16u : 0u;
+    nb.row[i] = !used ? 0u : ANY ? static_cast<uint32_t>(s.d * kEsz) : static_cast<uint32_t>(s.nchunks) * 16u;
     const int64_t own_tok = static_cast<int64_t>(ws.rank) * p.T + t;
     if constexpr (MODE == kFusedWait || MODE == kPublish) {
       const uintptr_t base = reinterpret_cast<uintptr_t>(p.slots[i]);
@@ -750,8 +946,10 @@ __device__ __forceinline__ void make_cursors(const KParams& p, const WaveSlice& 
 // alternate roles (the loop is unrolled by two) so that no copy forces a wait
 // on the requests in flight; past the last token the request goes through an
 // empty descriptor, so it is unconditional and fetches nothing.
-template <class F, int N0, int N1, int MODE, int SCHED>
+// ANY: rows of any width and alignment (schedule 0, modes without slots to wait for).
+template <class F, int N0, int N1, int MODE, int SCHED, bool ANY = false>
 __global__ __launch_bounds__(256) void qkn_rows(const KParams p) {
+  static_assert(!ANY || (SCHED == 0 && MODE <= kPartial), "rows of any alignment: one token per step, no waits");
   constexpr bool PF = (SCHED == 1);
   constexpr int M1 = N1 > 0 ? N1 : 1;
   const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
@@ -786,13 +984,18 @@ __global__ __launch_bounds__(256) void qkn_rows(const KParams p) {
   f32x4 g0[N0][kGammaVecs<F>];
   f32x4 g1[M1][kGammaVecs<F>];
   if constexpr (MODE != kPartial && MODE != kPublish) {
-    load_gamma<F, N0>(p.seg[0], ws.col0, lane, g0);
-    if constexpr (N1 > 0) load_gamma<F, N1>(p.seg[1], ws.col1, lane, g1);
+    if constexpr (ANY) {
+      load_gamma_any<F, N0>(p.seg[0].w, p.seg[0].d, lane, g0);
+      if constexpr (N1 > 0) load_gamma_any<F, N1>(p.seg[1].w, p.seg[1].d, lane, g1);
+    } else {
+      load_gamma<F, N0>(p.seg[0], ws.col0, lane, g0);
+      if constexpr (N1 > 0) load_gamma<F, N1>(p.seg[1], ws.col1, lane, g1);
+    }
   }
 
   Cursor c, dc;
   CursorBytes nb;
-  make_cursors<F, MODE>(p, ws, t, step, c, dc, nb);
+  make_cursors<F, MODE, ANY>(p, ws, t, step, c, dc, nb);
   TokenRegs<N0, M1> ra;
   if constexpr (SCHED >= 2) {
     static_assert(MODE == kFusedWait, "the publish-ahead schedules are wait-mode schedules");
@@ -855,7 +1058,7 @@ __global__ __launch_bounds__(256) void qkn_rows(const KParams p) {
     }
     return;
   } else {
-    fetch_token<F, N0, N1, MODE>(p, c, nb, lane, own_rank, ra);
+    fetch_token<F, N0, N1, MODE, true, ANY>(p, c, nb, lane, own_rank, ra);
   }
   if constexpr (PF) {
     TokenRegs<N0, M1> rb;
@@ -879,11 +1082,11 @@ __global__ __launch_bounds__(256) void qkn_rows(const KParams p) {
     }
   } else {
     while (true) {
-      process_token<F, N0, N1, MODE>(p, c, nb, lane, own_rank, g0, g1, ra, given_up);
+      process_token<F, N0, N1, MODE, ANY>(p, c, nb, lane, own_rank, g0, g1, ra, given_up);
       t += step;
       if (t >= end) break;
       advance(c, dc);
-      fetch_token<F, N0, N1, MODE>(p, c, nb, lane, own_rank, ra);
+      fetch_token<F, N0, N1, MODE, true, ANY>(p, c, nb, lane, own_rank, ra);
     }
   }
 }
@@ -897,21 +1100,6 @@ __global__ __launch_bounds__(256) void qkn_rows(const KParams p) {
 // staged in LDS once per workgroup and read from there in Phase C, which forms
 // (x * gamma) * factor -- the same operations, order and reduction tree as
 // every other path.
-
-// Phase C of one chunk: y = round((x * gamma) * inv), gamma from kGammaVecs<F> vectors.
-template <class F>
-__device__ __forceinline__ u32x4 scale_chunk(u32x4 v, const f32x4* g, float inv) {
-  constexpr int kG = kGammaVecs<F>;
-  f32x4 gq[kG];
-#pragma unroll
-  for (int j = 0; j < kG; ++j) gq[j] = g[j];
-  float f[F::kPer];
-  F::unpack(v, f);
-  float o[F::kPer];
-#pragma unroll
-  for (int e = 0; e < F::kPer; ++e) o[e] = (f[e] * gq[e >> 2][e & 3]) * inv;
-  return F::pack(o);
-}
 
 // Phase C of one wide row from gamma in LDS.
 template <class F, int N>
@@ -1104,6 +1292,10 @@ extern const RowsFn kApplyTable8[4];
 extern const RowsFn kPartialTable8[4];
 extern const RowsFn kFusedWaitTable8[5][4][5];
 extern const RowsFn kPublishTable8[4];
+// rows of any width and alignment up to the register path's widths, [N0 index][N1 index] and [N0 index]
+extern const RowsFn kAnyFusedTable[2][4][5];
+extern const RowsFn kAnyApplyTable[2][4];
+extern const RowsFn kAnyPartialTable[2][4];
 // general path [format][mode]; wide path [format][wide N0 index][mode][N1 index]
 extern const GenericFn kGenericTable[2][3];
 extern const RowsFn kWideTable[2][2][3][5];
