@@ -332,7 +332,9 @@ int qkn_last_launch(qkn_launch_info* info);
  *   "force_generic"  1 = always take the general path's staged kernel (same
  *                    results);
  *   "proj_tile"      qkn_proj_partial's kernel: 0 = automatic (split k for
- *                    decode-sized launches, else kernel 1), 1 = direct-to-
+ *                    decode-sized launches; else kernel 1, or 256 x 256 tiles
+ *                    of 512 threads with the same results where those are
+ *                    faster, reported under kernel 1's name), 1 = direct-to-
  *                    LDS two-stage kernel on 16 x 16 x 32 MFMAs, never split,
  *                    2 = register-staged kernel, never split, 3 = direct-to-
  *                    LDS kernel on 32 x 32 x 16 MFMAs, never split (2 and 3

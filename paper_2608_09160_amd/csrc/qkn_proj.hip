@@ -18,6 +18,8 @@
 //     (r mod 4) in accumulator r. Both walk k in ascending order per output,
 //     and the two instructions round their exact bf16 products identically:
 //     the results are bit-identical (checked on every tested shape).
+//   * Launches of many tiles take 256 x 256 tiles of eight wavefronts ("large
+//     tiles" below; the rule is at big_grid). Otherwise, and as kernel 1:
 //   * A 256-thread workgroup owns a 128 x 128 output tile (four wavefronts in
 //     2 x 2, 64 x 64 each = 4 x 4 or 2 x 2 MFMA blocks); k advances 64 at a time
 //     through two LDS stages that global memory fills directly (buffer_load
@@ -26,9 +28,9 @@
 //     row's 16-byte k-slots are XOR-swizzled so that the 16 rows a 16-lane
 //     group reads land on 16 distinct bank groups. Two such workgroups (64 KB
 //     of LDS each) share a CU. (Measured on MI355X against register-staged
-//     double buffering, three- and four-stage rings, k of 32 and 128 per stage
-//     and 256-wide tiles: this shape was the fastest; 16 x 16 x 32 MFMAs beat
-//     32 x 32 x 16 ones by 4-9 %.)
+//     double buffering, three- and four-stage rings, k of 32 and 128 per
+//     stage: this shape was the fastest of 128 x 128 tiles; 16 x 16 x 32 MFMAs
+//     beat 32 x 32 x 16 ones by 4-9 %.)
 //   * Global loads are raw buffer loads whose descriptors end at the last
 //     valid row, so rows past T or d_local read zeros; the k tail (hidden not
 //     a multiple of 64) is masked by moving the offset out of range.
@@ -82,6 +84,7 @@ constexpr int kGroupM = 8;                // row tiles per tile group
 constexpr int kXcds = 8;                  // MI355X: workgroup id mod 8 selects the XCD
 constexpr int kRsrcWord3 = 0x00020000;    // raw (untyped) buffer
 constexpr int kLdsBytes = 160 * 1024;     // LDS per CU on gfx950
+constexpr int kCus = 256;                 // MI355X
 
 struct ProjSegDev {
   const uint16_t* w;
@@ -93,6 +96,17 @@ struct ProjSegDev {
   int32_t tile0;         // first column tile of this segment in the launch
   int32_t nchunks;       // ceil(d / 128)
   int32_t col0;          // split-k: first column of this segment in the partial sums
+};
+
+// Work list of the large-tile kernel: `whole` 256 x 256 tiles, then `smalls`
+// 128 x 128 ones -- the quarters of the large tiles that would not fill a
+// round, the 128-column strips right of the large tiles, the row below them.
+struct BigGrid {
+  int32_t rows, cols[2];  // large tiles over tokens and over each segment's columns
+  int32_t bigs, whole;    // large tiles in all, and those computed as such
+  int32_t strip[2];       // a 128-column strip follows the segment's large tiles
+  int32_t strip_tiles;    // small tiles of the strips
+  int32_t smalls;         // small tiles in all
 };
 
 struct ProjParams {
@@ -111,6 +125,7 @@ struct ProjParams {
   int32_t kslice;        // k per slice, a multiple of the stage k
   float* part;
   int32_t ncols;         // columns of both segments
+  BigGrid big;           // large-tile kernel
 };
 
 __device__ __forceinline__ Rsrc make_rsrc(const void* base, uint32_t bytes) {
@@ -165,7 +180,7 @@ __device__ __forceinline__ bool tile_of(int bid, int grid, int m_tiles, const Pr
 // bf16, stage the tile in LDS (`lds`, at least BM x OUT_ROW bf16; the caller
 // has finished with it), write it to y with coalesced 16-byte stores, and
 // take the Phase A statistic of each row's 128-column chunks.
-template <int BM, int BN, int OUT_ROW>
+template <int BM, int BN, int OUT_ROW, int THREADS = kThreads>
 __device__ __forceinline__ void epilogue_staged(const ProjParams& p, const ProjSegDev& s,
                                                 const uint16_t* out, int64_t m0, int n0,
                                                 int rows_a, int rows_b);
@@ -227,7 +242,7 @@ __device__ __forceinline__ void epilogue16(const ProjParams& p, const ProjSegDev
 }
 
 // Stores and statistic of a tile staged in LDS as bf16 ([BM][OUT_ROW]).
-template <int BM, int BN, int OUT_ROW>
+template <int BM, int BN, int OUT_ROW, int THREADS>
 __device__ __forceinline__ void epilogue_staged(const ProjParams& p, const ProjSegDev& s,
                                                 const uint16_t* out, int64_t m0, int n0,
                                                 int rows_a, int rows_b) {
@@ -238,8 +253,8 @@ __device__ __forceinline__ void epilogue_staged(const ProjParams& p, const ProjS
   const Rsrc ry = make_rsrc(s.y + m0 * s.ldy + n0, y_bytes);
   constexpr int kRowVecs = BN / 8;
 #pragma unroll
-  for (int i = 0; i < BM * kRowVecs / kThreads; ++i) {
-    const int v = tid + kThreads * i;
+  for (int i = 0; i < BM * kRowVecs / THREADS; ++i) {
+    const int v = tid + THREADS * i;
     const int row = v / kRowVecs, cv = (v % kRowVecs) * 8;
     const u32x4 val = *reinterpret_cast<const u32x4*>(out + row * OUT_ROW + cv);
     st16(val, ry, cv < rows_b ? static_cast<uint32_t>((row * s.ldy + cv) * 2) : y_bytes);
@@ -250,8 +265,8 @@ __device__ __forceinline__ void epilogue_staged(const ProjParams& p, const ProjS
   constexpr int kUnits = BM * (BN / kChunkN) * 2;
   static_assert(kUnits % 64 == 0, "whole wavefronts of units");
 #pragma unroll
-  for (int it = 0; it < (kUnits + kThreads - 1) / kThreads; ++it) {
-    const int u = tid + kThreads * it;
+  for (int it = 0; it < (kUnits + THREADS - 1) / THREADS; ++it) {
+    const int u = tid + THREADS * it;
     const bool live = u < kUnits;  // a 64-row tile has units for half the threads
     const int half = u & 1, rc = u >> 1;
     const int row = rc % BM, chunk = rc / BM;
@@ -612,6 +627,274 @@ __device__ __forceinline__ void dl_mainloop(const ProjParams& p, const ProjSegDe
 #undef QKN_ISSUE_STAGE
 }
 
+// ------------------------------------------------------------------ large tiles
+//
+// Whole-tile launches on 256 x 256 output tiles: eight wavefronts (2 x 4, two
+// per SIMD), each 128 x 64 = 8 x 4 blocks of 16 x 16 x 32 MFMAs, 128 fp32
+// accumulators per lane. What this is for: the 128 x 128 tile with 64 x 64
+// per wavefront reads 64 KB of LDS and fills 32 KB per 512 MFMA cycles of a
+// k-stage, more than the 128 bytes per cycle that LDS moves; the 256 x 256
+// tile needs 192 + 64 KB per 2048 cycles, and half the bytes from L2 per
+// product. Per stage of 64 k:
+//   * Two LDS stages (64 KB each), filled directly from global memory with
+//     whole 128-byte row pieces (64-byte pieces, k 32 per stage in a ring of
+//     four, cost 10 %: every line came out of L2 twice).
+//   * Fragments are double-buffered in registers by halves of 32 k: while one
+//     half's 32 MFMAs run, the 12 LDS reads of the next half go out, one
+//     after every second MFMA. The last half of a stage is in registers when
+//     its first half's MFMAs end, so the one barrier per stage then frees the
+//     stage for the loads two stages ahead, which have two halves' time to land.
+//   * The operands are swapped in the MFMA (W rows as its rows), so that a
+//     lane ends with four adjacent columns of one token: 8-byte LDS writes in
+//     the epilogue instead of 2-byte ones. Every output still takes k in
+//     ascending blocks of 32: the bits are those of the 128 x 128 kernel.
+// Measured (8192 tokens, hidden 4096): 2048 columns, 256 tiles: 110 us against
+// 144; 2048 + 512 columns: 157 us against 205; from 4096 to 8192 hidden the
+// time grows at 1.40 PF/s (the library GEMM: 1.56). Without its loads the same
+// loop runs at 1.55 PF/s and with every load an L2 hit at 1.45: the LDS write
+// port and L2 set the rest. Four wavefronts of 128 x 128 (one per SIMD, so
+// nothing covers a wait) took 155-160 us, loads spread between the LDS reads
+// and raised wave priorities changed nothing.
+template <int TM, int TN, int S_>
+struct BigCfg {
+  static constexpr int S = S_;                               // LDS stages
+  static constexpr int kWr = 2, kWc = 4;                     // wavefronts over the tile's rows and columns
+  static constexpr int kWaves = kWr * kWc;
+  static constexpr int BK = 64;
+  static constexpr int kBytesA = TM * BK * 2;
+  static constexpr int kBytesB = TN * BK * 2;
+  static constexpr int kStage = kBytesA + kBytesB;
+  static constexpr int kLoadsA = kBytesA / 1024 / kWaves;    // 1 KB load instructions per wavefront
+  static constexpr int kLoadsB = kBytesB / 1024 / kWaves;
+  static constexpr int kLoads = kLoadsA + kLoadsB;
+  static constexpr int kMi = TM / kWr / 16, kNi = TN / kWc / 16;  // MFMA blocks per wavefront
+  static constexpr int kOutRow = TN + 8;
+  static constexpr int kLds = (S * kStage > TM * kOutRow * 2) ? S * kStage : TM * kOutRow * 2;
+  static_assert(kLoadsA * 1024 * kWaves == kBytesA && kLoadsB * 1024 * kWaves == kBytesB, "whole loads");
+  static_assert(kLoadsA % 2 == 0 && kLoadsB % 2 == 0, "a wavefront's loads start at a multiple of 16 rows");
+  static_assert(S == 2 || S == 4, "the stage loop is unrolled by S");
+  static_assert(kLds <= kLdsBytes, "LDS");
+};
+
+constexpr int kBigThreads = 64 * BigCfg<256, 256, 2>::kWaves;
+
+__device__ __forceinline__ void load16_to_lds_at(Rsrc r, LdsByte* dst, uint32_t voff, uint32_t soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, voff, soff, 0, 0);
+}
+
+__device__ __forceinline__ bf16x8 lds_frag(LdsByte* at) {
+  return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(at);
+}
+
+// Main loop of one tile of TM rows from m0 (rows_a valid) by TN columns from
+// n0 of segment s (rows_b valid), k in [k_lo, k_hi). acc[i][j], lane l: token
+// 16 i + l mod 16, columns 16 j + 4 (l / 16) + r of the wavefront's share.
+template <int TM, int TN, int S>
+__device__ __forceinline__ void big_mainloop(const ProjParams& p, const ProjSegDev& s, unsigned char* lds,
+                                             int64_t m0, int n0, int rows_a, int rows_b, int k_lo, int k_hi,
+                                             f32x4 (&acc)[BigCfg<TM, TN, S>::kMi][BigCfg<TM, TN, S>::kNi]) {
+  using C = BigCfg<TM, TN, S>;
+  const int tid = static_cast<int>(threadIdx.x);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / C::kWc, wn = wave % C::kWc;
+  const uint32_t a_bytes = static_cast<uint32_t>(rows_a * p.ldx * 2);
+  const uint32_t b_bytes = static_cast<uint32_t>(rows_b * s.ldw * 2);
+  const Rsrc ra = make_rsrc(p.x + m0 * p.ldx, a_bytes);
+  const Rsrc rb = make_rsrc(s.w + static_cast<int64_t>(n0) * s.ldw, b_bytes);
+  // A load instruction fills 8 rows of 128 bytes; a row's eight 16-byte slots
+  // are swizzled by (row / 2) mod 8, as in the 128 x 128 kernel.
+  const int kv[2] = {((lane & 7) ^ (lane >> 4)) * 8, (((lane & 7) ^ (lane >> 4)) * 8) ^ 32};
+  // offsets of a wavefront's first two loads of each operand; the others follow in steps of 16 rows
+  uint32_t va[2], vb[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    va[i] = static_cast<uint32_t>(((wave * C::kLoadsA + i) * 8 + (lane >> 3)) * p.ldx * 2) + kv[i] * 2;
+    vb[i] = static_cast<uint32_t>(((wave * C::kLoadsB + i) * 8 + (lane >> 3)) * s.ldw * 2) + kv[i] * 2;
+  }
+  const uint32_t step_a = static_cast<uint32_t>(32 * p.ldx), step_b = static_cast<uint32_t>(32 * s.ldw);
+  const int nk = (k_hi - k_lo + C::BK - 1) / C::BK;
+  // Stage kt into ring slot `slot`. k-vectors past k_hi, and whole stages past
+  // the last, read zeros through an offset behind the descriptor; the scalar
+  // offset stays within one row, since the range check subtracts it.
+  auto issue = [&](int slot, int kt) __attribute__((always_inline)) {
+    const bool live = kt < nk;
+    const int k0 = live ? k_lo + kt * C::BK : 0;
+    const bool ok[2] = {live && k0 + kv[0] < k_hi, live && k0 + kv[1] < k_hi};
+    LdsByte* base = (LdsByte*)(lds + slot * C::kStage);
+#pragma unroll
+    for (int n = 0; n < C::kLoadsA; ++n)
+      load16_to_lds_at(ra, base + (wave * C::kLoadsA + n) * 1024,
+                       ok[n & 1] ? va[n & 1] + (n >> 1) * step_a : a_bytes, k0 * 2);
+#pragma unroll
+    for (int n = 0; n < C::kLoadsB; ++n)
+      load16_to_lds_at(rb, base + C::kBytesA + (wave * C::kLoadsB + n) * 1024,
+                       ok[n & 1] ? vb[n & 1] + (n >> 1) * step_b : b_bytes, k0 * 2);
+  };
+  // This lane's fragment addresses per ring slot and k-half, hidden from the
+  // compiler so that a block's offset goes into the instruction (it would
+  // otherwise keep one address register per fragment).
+  const int fr = lane & 15;
+  const int fslot = ((lane >> 4) ^ (fr >> 1)) * 16;  // the second half's slot: ^ 64 bytes
+  LdsByte* fa[S][2];
+  LdsByte* fb[S][2];
+#pragma unroll
+  for (int q = 0; q < S; ++q)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      fa[q][h] = (LdsByte*)lds + q * C::kStage + (wm * (TM / C::kWr) + fr) * 128 + (fslot ^ (64 * h));
+      fb[q][h] = (LdsByte*)lds + q * C::kStage + C::kBytesA + (wn * (TN / C::kWc) + fr) * 128 +
+                 (fslot ^ (64 * h));
+      asm volatile("" : "+v"(fa[q][h]), "+v"(fb[q][h]));
+    }
+#pragma unroll
+  for (int i = 0; i < C::kMi; ++i)
+#pragma unroll
+    for (int j = 0; j < C::kNi; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+  bf16x8 A[2][C::kMi], B[2][C::kNi];
+#pragma unroll
+  for (int q = 0; q < S; ++q) issue(q, q);
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 1) * C::kLoads));
+  __builtin_amdgcn_s_barrier();
+#define QKN_BIG_READ(set, slot, half)                                                                    \
+  _Pragma("unroll") for (int j = 0; j < C::kNi; ++j) B[set][j] = lds_frag(fb[slot][half] + j * 2048);    \
+  _Pragma("unroll") for (int i = 0; i < C::kMi; ++i) A[set][i] = lds_frag(fa[slot][half] + i * 2048)
+  // 32 MFMAs of one half, an LDS read of the next half after every second one
+#define QKN_BIG_MFMA(set)                                                                                \
+  _Pragma("unroll") for (int i = 0; i < C::kMi; ++i)                                                     \
+      _Pragma("unroll") for (int j = 0; j < C::kNi; ++j) acc[i][j] =                                     \
+          __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[set][j], A[set][i], acc[i][j], 0, 0, 0);             \
+  _Pragma("unroll") for (int g = 0; g < C::kMi + C::kNi; ++g) {                                          \
+    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                                   \
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                                   \
+  }                                                                                                      \
+  __builtin_amdgcn_sched_group_barrier(0x008, C::kMi * C::kNi, 0);                                       \
+  __builtin_amdgcn_sched_barrier(0)
+  // Stage kt + q in ring slot q. At the barrier every wavefront has its second
+  // half in registers (lgkmcnt 0) and its part of the next stage in LDS (at
+  // most the S - 2 stages after that in flight), so slot q takes stage kt + q + S.
+#define QKN_BIG_STAGE(q)                                                                                 \
+  {                                                                                                      \
+    QKN_BIG_READ(1, q, 1);                                                                               \
+    QKN_BIG_MFMA(0);                                                                                     \
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * C::kLoads) & ~0x0F00);                                \
+    __builtin_amdgcn_s_barrier();                                                                        \
+    __builtin_amdgcn_sched_barrier(0);                                                                   \
+    issue(q, kt + (q) + S);                                                                              \
+    QKN_BIG_READ(0, ((q) + 1) % S, 0);                                                                   \
+    QKN_BIG_MFMA(1);                                                                                     \
+  }
+  QKN_BIG_READ(0, 0, 0);
+  for (int kt = 0; kt < nk; kt += S) {  // stages past nk multiply zeros
+    QKN_BIG_STAGE(0);
+    QKN_BIG_STAGE(1);
+    if constexpr (S == 4) {
+      if (kt + 2 >= nk) break;
+      QKN_BIG_STAGE(2);
+      QKN_BIG_STAGE(3);
+    }
+  }
+#undef QKN_BIG_STAGE
+#undef QKN_BIG_MFMA
+#undef QKN_BIG_READ
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the caller reuses the stages: no load may land in them
+  __syncthreads();
+}
+
+// One tile with its epilogue.
+template <int TM, int TN, int S>
+__device__ __forceinline__ void big_tile(const ProjParams& p, const ProjSegDev& s, unsigned char* lds,
+                                         int64_t m0, int n0, int rows_a, int rows_b) {
+  using C = BigCfg<TM, TN, S>;
+  f32x4 acc[C::kMi][C::kNi];
+  big_mainloop<TM, TN, S>(p, s, lds, m0, n0, rows_a, rows_b, 0, p.hidden, acc);
+  const int tid = static_cast<int>(threadIdx.x);
+  const int lane = tid & 63, wave = tid >> 6;
+  const int wm = wave / C::kWc, wn = wave % C::kWc;
+  uint16_t* out = reinterpret_cast<uint16_t*>(lds);  // [TM][kOutRow]
+#pragma unroll
+  for (int i = 0; i < C::kMi; ++i)
+#pragma unroll
+    for (int j = 0; j < C::kNi; ++j) {
+      const int row = wm * (TM / C::kWr) + i * 16 + (lane & 15);
+      const int col = wn * (TN / C::kWc) + j * 16 + 4 * (lane >> 4);
+      const uint64_t v = (static_cast<uint64_t>(pack_bf16x2(acc[i][j][2], acc[i][j][3])) << 32) |
+                         pack_bf16x2(acc[i][j][0], acc[i][j][1]);
+      *reinterpret_cast<uint64_t*>(out + row * C::kOutRow + col) = v;
+    }
+  __syncthreads();
+  epilogue_staged<TM, TN, C::kOutRow, kBigThreads>(p, s, out, m0, n0, rows_a, rows_b);
+}
+
+// Position `l` of block b among n blocks dealt round-robin over the XCDs, so that each XCD takes a
+// contiguous run of the n positions.
+__device__ __forceinline__ int xcd_run(int b, int n) {
+  const int x = b % kXcds, per = n / kXcds, extra = n % kXcds;
+  return x * per + (x < extra ? x : extra) + b / kXcds;
+}
+
+// The work list of BigGrid, one tile per workgroup. The small tiles run the
+// same loop with 64 x 32 per wavefront and a ring of four stages.
+constexpr int kBigLds = BigCfg<256, 256, 2>::kLds;
+static_assert(BigCfg<128, 128, 4>::kLds <= kBigLds, "LDS of the small tiles");
+__global__ __launch_bounds__(kBigThreads, 2) void qkn_proj_gemm_big(const ProjParams p) {
+  __shared__ __align__(1024) unsigned char lds[kBigLds];
+  const BigGrid& g = p.big;
+  const int bid = static_cast<int>(blockIdx.x);
+  int row = 0, col = 0, si = 0;  // tile origin: token, column of segment si
+  bool small = true;
+  int big = -1, quad = 0, l = 0;
+  if (bid < g.whole) {
+    big = xcd_run(bid, g.whole);
+    small = false;
+  } else {
+    l = xcd_run(bid - g.whole, g.smalls);
+    if (l < 4 * (g.bigs - g.whole)) {
+      big = g.whole + l / 4;
+      quad = l % 4;
+    } else {
+      l -= 4 * (g.bigs - g.whole);
+    }
+  }
+  if (big >= 0) {
+    const int nb = g.cols[0] + g.cols[1];
+    const int group = big / (kGroupM * nb), first = group * kGroupM;
+    const int gm = (g.rows - first < kGroupM) ? g.rows - first : kGroupM;
+    const int in = big - group * kGroupM * nb;
+    const int nt = in / gm;
+    si = nt >= g.cols[0] ? 1 : 0;
+    row = (first + in % gm) * 256 + (quad & 1) * 128;
+    col = (si ? nt - g.cols[0] : nt) * 256 + (quad >> 1) * 128;
+  } else if (l < g.strip_tiles) {
+    // 128-column strips right of the large tiles, first segment's first
+    const int per = 2 * g.rows;
+    si = (g.strip[0] && l < per) ? 0 : 1;
+    row = (l % per) * 128;
+    col = g.cols[si] * 256;
+  } else {
+    // the row of small tiles below them
+    l -= g.strip_tiles;
+    const int n0 = (p.seg[0].d + 127) / 128;
+    si = l >= n0 ? 1 : 0;
+    row = g.rows * 256;
+    col = (si ? l - n0 : l) * 128;
+  }
+  row = __builtin_amdgcn_readfirstlane(row);
+  col = __builtin_amdgcn_readfirstlane(col);
+  si = __builtin_amdgcn_readfirstlane(si);
+  const ProjSegDev& s = p.seg[si];
+  const int64_t left = p.T - row;
+  const int right = s.d - col;
+  if (left <= 0 || right <= 0) return;  // a quarter or a strip tile outside the output
+  if (!small)
+    big_tile<256, 256, 2>(p, s, lds, row, col, static_cast<int>(left < 256 ? left : 256),
+                          right < 256 ? right : 256);
+  else
+    big_tile<128, 128, 4>(p, s, lds, row, col, static_cast<int>(left < 128 ? left : 128),
+                          right < 128 ? right : 128);
+}
+
 // The segment, origin and valid extent of output tile (row tile mt of height
 // 64 WMB from row `row0`, column tile nt over both segments).
 struct TileAt {
@@ -901,6 +1184,44 @@ Plan plan_of(int64_t T, int64_t hidden, const qkn_proj_seg* segs, int nseg) {
   return pl;
 }
 
+// Costs of one round over the CUs in hundredths of a round of 256 x 256 tiles
+// (one per CU): 128 x 128 tiles of the large-tile kernel (one per CU) 35,
+// 128 x 128 tiles of the two-stage kernel (two per CU) 60. Measured at hidden
+// 4096: rounds of 98, 31-36 and 57-61 us; so up to 256 small tiles the
+// large-tile kernel's are 1.4-1.6 times as fast (33 against 51 us for 1536
+// tokens x 1280 columns), for 257 to 512 the two-stage kernel's two per CU win
+// (57 against 62 us), and beyond, large tiles are 1.25-1.35 times as fast.
+constexpr int kRoundBig = 100, kRoundSmall = 35, kRoundOld = 60;
+
+// Large tiles cover every 256-block that is at least half full. Those of an
+// incomplete last round are computed as quarters where that takes less time.
+BigGrid big_grid(int64_t T, const qkn_proj_seg* segs, int nseg, int* cost) {
+  const auto rounds = [](int64_t n) { return static_cast<int>((n + kCus - 1) / kCus); };
+  BigGrid g{};
+  const int64_t rest = T % 256;
+  g.rows = static_cast<int32_t>(T / 256 + (rest > 128 ? 1 : 0));
+  int64_t n128 = 0;
+  for (int i = 0; i < nseg; ++i) {
+    const int64_t d = segs[i].d_local, r = d % 256;
+    g.cols[i] = static_cast<int32_t>(d / 256 + (r > 128 ? 1 : 0));
+    g.strip[i] = (r > 0 && r <= 128) ? 1 : 0;
+    g.strip_tiles += g.strip[i] * 2 * g.rows;
+    n128 += (d + 127) / 128;
+  }
+  g.bigs = g.rows * (g.cols[0] + g.cols[1]);
+  const int64_t other = g.strip_tiles + (rest > 0 && rest <= 128 ? n128 : 0);
+  const int rem = g.bigs % kCus;
+  const int full = kRoundBig * (g.bigs / kCus);
+  // CUs without a large tile in its last round take two small ones meanwhile
+  const int64_t beside = rem ? 2 * (kCus - rem) : 0;
+  const int as_big = full + (rem ? kRoundBig : 0) + kRoundSmall * rounds(other > beside ? other - beside : 0);
+  const int as_small = full + kRoundSmall * rounds(int64_t{4} * rem + other);
+  g.whole = g.bigs - (as_small < as_big ? rem : 0);
+  g.smalls = static_cast<int32_t>(int64_t{4} * (g.bigs - g.whole) + other);
+  *cost = as_small < as_big ? as_small : as_big;
+  return g;
+}
+
 // ---------------------------------------------------------------- workspace without allocation
 //
 // The entry point for callers that cannot allocate (HIP graph capture, tight
@@ -1050,7 +1371,21 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
     if (tiles > max_wgs) return QKN_ENOTSUP;
     grid = round8(tiles);
   }
-  const qkn_launch_info info{name, grid, kThreads, grid * (kThreads / 64), lds};
+  int block = kThreads;
+  if (!split && g_tile_choice == 0) {
+    // the large-tile kernel where it is faster; it reports kernel 1's name,
+    // whose results it gives bit for bit (512 threads tell it apart)
+    int cost = 0;
+    p.big = big_grid(T, segs, nseg, &cost);
+    const int64_t tiles = static_cast<int64_t>(p.m_tiles) * p.n_tiles;
+    if (cost < kRoundOld * ((tiles + 2 * kCus - 1) / (2 * kCus))) {
+      gemm = reinterpret_cast<const void*>(qkn_proj_gemm_big);
+      grid = static_cast<int64_t>(p.big.whole) + p.big.smalls;
+      block = kBigThreads;
+      lds = kBigLds;
+    }
+  }
+  const qkn_launch_info info{name, grid, block, grid * (block / 64), lds};
   if (qkn_host::validate_only()) {
     qkn_host::record_launch(qkn_launch_info{info.kernel, 0, 0, 0, info.lds_bytes});
     return QKN_EDRYRUN;
@@ -1064,7 +1399,7 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
   for (int i = 0; i < nseg; ++i) p.seg[i].tile_partials = split ? nullptr : ws + ws_off[i];
   hipStream_t st = static_cast<hipStream_t>(stream);
   void* args[] = {&p};
-  if (hipLaunchKernel(gemm, dim3(static_cast<unsigned>(grid)), dim3(kThreads), args, 0, st) !=
+  if (hipLaunchKernel(gemm, dim3(static_cast<unsigned>(grid)), dim3(block), args, 0, st) !=
       hipSuccess)
     return QKN_EHIP;
   if (split) {
