@@ -45,10 +45,10 @@
 //     statistics of each token in ascending tile order.
 //   * Decode-sized launches (at most 8 row tiles, which alone would leave most
 //     CUs idle) split k: separate workgroups take contiguous k-slices of each
-//     tile (64-row tiles up to 64 tokens; four LDS stages, so a slice's loads
-//     are all in flight at once) and store their fp32 sums; one reduction
-//     launch, a workgroup per token and segment, adds the slices in ascending order,
-//     rounds once, writes y and takes the statistic with the same tree.
+//     tile and store their fp32 sums; one reduction launch, a workgroup per
+//     token and segment, adds the slices in ascending order, rounds once,
+//     writes y and takes the statistic with the same tree. Up to 64 tokens on
+//     64-row tiles, all of a slice's loads in flight at once.
 
 #include <hip/hip_runtime.h>
 
@@ -671,7 +671,7 @@ struct BigCfg {
   static constexpr int kOutRow = TN + 8;
   static constexpr int kLds = (S * kStage > TM * kOutRow * 2) ? S * kStage : TM * kOutRow * 2;
   static_assert(kLoadsA * 1024 * kWaves == kBytesA && kLoadsB * 1024 * kWaves == kBytesB, "whole loads");
-  static_assert(kLoadsA % 2 == 0 && kLoadsB % 2 == 0, "a wavefront's loads start at a multiple of 16 rows");
+  static_assert((kLoadsA == 1 || kLoadsA % 2 == 0) && kLoadsB % 2 == 0, "the slots' swizzle of a load is known");
   static_assert(S == 2 || S == 4, "the stage loop is unrolled by S");
   static_assert(kLds <= kLdsBytes, "LDS");
 };
@@ -705,11 +705,13 @@ __device__ __forceinline__ void big_mainloop(const ProjParams& p, const ProjSegD
   // A load instruction fills 8 rows of 128 bytes; a row's eight 16-byte slots
   // are swizzled by (row / 2) mod 8, as in the 128 x 128 kernel.
   const int kv[2] = {((lane & 7) ^ (lane >> 4)) * 8, (((lane & 7) ^ (lane >> 4)) * 8) ^ 32};
+  const int kva0 = (C::kLoadsA == 1 && (wave & 1)) ? kv[1] : kv[0];  // a wavefront's first x rows: 8 wave, or 16 n
   // offsets of a wavefront's first two loads of each operand; the others follow in steps of 16 rows
   uint32_t va[2], vb[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    va[i] = static_cast<uint32_t>(((wave * C::kLoadsA + i) * 8 + (lane >> 3)) * p.ldx * 2) + kv[i] * 2;
+    va[i] = static_cast<uint32_t>(((wave * C::kLoadsA + i) * 8 + (lane >> 3)) * p.ldx * 2) +
+            (i == 0 ? kva0 : kv[1]) * 2;
     vb[i] = static_cast<uint32_t>(((wave * C::kLoadsB + i) * 8 + (lane >> 3)) * s.ldw * 2) + kv[i] * 2;
   }
   const uint32_t step_a = static_cast<uint32_t>(32 * p.ldx), step_b = static_cast<uint32_t>(32 * s.ldw);
@@ -717,15 +719,16 @@ __device__ __forceinline__ void big_mainloop(const ProjParams& p, const ProjSegD
   // Stage kt into ring slot `slot`. k-vectors past k_hi, and whole stages past
   // the last, read zeros through an offset behind the descriptor; the scalar
   // offset stays within one row, since the range check subtracts it.
-  auto issue = [&](int slot, int kt) __attribute__((always_inline)) {
+  auto issue = [=](int slot, int kt) __attribute__((always_inline)) {
     const bool live = kt < nk;
     const int k0 = live ? k_lo + kt * C::BK : 0;
     const bool ok[2] = {live && k0 + kv[0] < k_hi, live && k0 + kv[1] < k_hi};
+    const bool oka0 = live && k0 + kva0 < k_hi;
     LdsByte* base = (LdsByte*)(lds + slot * C::kStage);
 #pragma unroll
     for (int n = 0; n < C::kLoadsA; ++n)
       load16_to_lds_at(ra, base + (wave * C::kLoadsA + n) * 1024,
-                       ok[n & 1] ? va[n & 1] + (n >> 1) * step_a : a_bytes, k0 * 2);
+                       ((n & 1) ? ok[1] : oka0) ? va[n & 1] + (n >> 1) * step_a : a_bytes, k0 * 2);
 #pragma unroll
     for (int n = 0; n < C::kLoadsB; ++n)
       load16_to_lds_at(rb, base + C::kBytesA + (wave * C::kLoadsB + n) * 1024,
@@ -947,11 +950,74 @@ __global__ __launch_bounds__(kThreads) void qkn_proj_gemm_dl(const ProjParams p)
   dl_tile<MI, 2, BK, S>(p, lds, 0, mt, nt);
 }
 
-// Split k: workgroup b takes k-slice b mod splits of tile b / splits (tiles
-// of 64 WMB rows) and stores its fp32 sums into the slice array instead of
+constexpr int kSplitBk = 64;
+constexpr int kSplitStages = 4;  // a 256-deep slice has all its loads in flight at once
+
+// Stores a wavefront's share of a tile's fp32 sums into an fp32 tile in LDS.
+template <class C>
+__device__ __forceinline__ void acc_to_lds(const f32x4 (&acc)[C::kMi][C::kNi], float* tile, int row_len, int row0,
+                                           int col0, int lane) {
+#pragma unroll
+  for (int i = 0; i < C::kMi; ++i)
+#pragma unroll
+    for (int j = 0; j < C::kNi; ++j)
+      *reinterpret_cast<f32x4*>(tile + (row0 + i * 16 + (lane & 15)) * row_len + col0 + j * 16 + 4 * (lane >> 4)) =
+          acc[i][j];
+}
+
+// Split k: a workgroup takes one k-slice of one TM x 128 tile with the
+// large-tile kernel's loop and stores its fp32 sums into the slice array
+// instead of running the epilogue. Bound by LDS like the small tiles there
+// (0.41 us per stage of 64 k) plus 6 us of first loads, stores and launch.
+// Against four wavefronts of 64 x 64 without fragments ahead and with each
+// XCD's workgroups spread over all tiles (so that every XCD's L2 fetched
+// nearly all of x and W): 777 tokens, hidden 5120, 1536 columns 33.4 -> 24.8 us.
+template <int TM, int S>
+__global__ __launch_bounds__(kBigThreads, S == 2 ? 4 : 2) void qkn_proj_gemm_split(const ProjParams p) {
+  using C = BigCfg<TM, 128, S>;
+  constexpr int kRow = 128 + 4;  // fp32 per row of the tile staged for the stores
+  constexpr int kLds = C::kLds > TM * kRow * 4 ? C::kLds : TM * kRow * 4;
+  __shared__ __align__(1024) unsigned char lds[kLds];
+  const int b = xcd_run(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+  // slice-major runs: an XCD's workgroups share the slice's columns of x and W
+  const int tiles = p.m_tiles * p.n_tiles;
+  const int ks = b / tiles;
+  int mt, nt;
+  if (!tile_from(b - ks * tiles, p.m_tiles, p, mt, nt)) return;
+  const int k_lo = ks * p.kslice;
+  const int k_hi = (k_lo + p.kslice < p.hidden) ? k_lo + p.kslice : p.hidden;
+  mt = __builtin_amdgcn_readfirstlane(mt);
+  nt = __builtin_amdgcn_readfirstlane(nt);
+  const ProjSegDev s = (p.nseg == 2 && nt >= p.seg[1].tile0) ? p.seg[1] : p.seg[0];
+  const int64_t m0 = static_cast<int64_t>(mt) * TM;
+  const int n0 = (nt - s.tile0) * 128;
+  const int rows_a = static_cast<int>((p.T - m0 < TM) ? p.T - m0 : TM);
+  const int rows_b = (s.d - n0 < 128) ? s.d - n0 : 128;
+  f32x4 acc[C::kMi][C::kNi];
+  big_mainloop<TM, 128, S>(p, s, lds, m0, n0, rows_a, rows_b, k_lo, k_hi, acc);
+  // through LDS, to write rows out in 16-byte vectors of adjacent lanes
+  const int tid = static_cast<int>(threadIdx.x);
+  const int wave = tid >> 6;
+  float* tile = reinterpret_cast<float*>(lds);
+  acc_to_lds<C>(acc, tile, kRow, (wave / C::kWc) * (TM / C::kWr), (wave % C::kWc) * 32, tid & 63);
+  __syncthreads();
+  // a row's valid columns are a multiple of 8 (d_local is), and its first
+  // column's offset in the slice array is a multiple of 8 floats, so every
+  // vector is whole and 16-byte aligned
+  float* part = p.part + static_cast<int64_t>(ks) * p.T * p.ncols + m0 * p.ncols + s.col0 + n0;
+  for (int q = tid; q < TM * 32; q += kBigThreads) {
+    const int row = q / 32, c4 = (q % 32) * 4;
+    if (row < rows_a && c4 < rows_b)
+      *reinterpret_cast<f32x4*>(part + static_cast<int64_t>(row) * p.ncols + c4) =
+          *reinterpret_cast<const f32x4*>(tile + row * kRow + c4);
+  }
+}
+
+// Split k, up to 64 tokens and one workgroup per CU: workgroup b takes k-slice
+// b mod splits of the 64-row tile b / splits and stores its fp32 sums into the slice array instead of
 // running the epilogue.
-template <int WMB, int BK, int S>
-__global__ __launch_bounds__(kThreads) void qkn_proj_gemm_split(const ProjParams p) {
+__global__ __launch_bounds__(kThreads) void qkn_proj_gemm_decode(const ProjParams p) {
+  constexpr int WMB = 1, BK = kSplitBk, S = kSplitStages;
   constexpr int MI = 16;  // 16 x 16 x 32 MFMAs (same bits as 32 x 32 x 16, 1-2 % faster here)
   using C = DlCfg<WMB, BK, S>;
   __shared__ __align__(1024) unsigned char lds[C::kLdsBytes];
@@ -1073,6 +1139,72 @@ __global__ __launch_bounds__(64 * kReduceWaves) void qkn_proj_reduce(const ProjP
   }
 }
 
+// The same reduction for launches of many workgroups (more than two per CU),
+// where the chains would bound it if every wavefront ran its own chunk's (64
+// LDS reads and FMAs on every wavefront): each round's stored values stay in
+// LDS, and after the barrier wavefront 0 runs all of the round's chains, two
+// lanes per chunk. LDS rows are padded so that the lanes' 16-byte reads use
+// different banks. 777 tokens x 1536 columns, two slices: 6.3 -> 5.5 us; 64
+// tokens: 0.3 us longer than the kernel above, since the chains then wait for
+// the slowest wavefront's loads.
+constexpr int kHalf = kChunkN / 2 + 4;  // floats per staged half chunk
+template <int SPLITS>
+__global__ __launch_bounds__(64 * kReduceWaves) void qkn_proj_reduce_many(const ProjParams p) {
+  __shared__ __align__(16) float vals[2][kReduceWaves][2][kHalf];
+  const int64_t t = blockIdx.x;
+  const int si = static_cast<int>(blockIdx.y);
+  const ProjSegDev& s = p.seg[si];
+  const int tid = static_cast<int>(threadIdx.x);
+  const int lane = tid & 63, wave = tid >> 6;
+  const int waves = static_cast<int>(blockDim.x) >> 6;
+  const int64_t slice = p.T * p.ncols;
+  float S = 0.0f;
+  for (int q0 = 0, round = 0; q0 < s.nchunks; q0 += waves, ++round) {
+    const int c = (q0 + wave) * kChunkN + 2 * lane;  // d_local is a multiple of 8: c < d means c + 1 < d
+    f32x2 v = {0.0f, 0.0f};                          // columns past d_local hold 0, which adds nothing
+    if (c < s.d) {
+      const float* src = p.part + t * p.ncols + s.col0 + c;
+      f32x2 b[SPLITS];  // every slice's load in flight before the first add
+#pragma unroll
+      for (int k = 0; k < SPLITS; ++k) b[k] = *reinterpret_cast<const f32x2*>(src + k * slice);
+      f32x2 a = b[0];
+#pragma unroll
+      for (int k = 1; k < SPLITS; ++k) {
+        a[0] = a[0] + b[k][0];
+        a[1] = a[1] + b[k][1];
+      }
+      const uint32_t pk = pack_bf16x2(a[0], a[1]);
+      *reinterpret_cast<uint32_t*>(s.y + t * s.ldy + c) = pk;
+      v = f32x2{bf16_lo(pk), bf16_hi(pk)};
+    }
+    *reinterpret_cast<f32x2*>(&vals[round & 1][wave][lane >> 5][2 * (lane & 31)]) = v;
+    // one barrier a round: wavefront 0 reads a round's rows before it reaches
+    // the next barrier, and the round after that one is the first to write them
+    __syncthreads();
+    if (wave == 0) {
+      const int n = s.nchunks - q0 < waves ? s.nchunks - q0 : waves;
+      const int mine = lane >> 1 < n ? lane >> 1 : 0;  // lanes 2 i, 2 i + 1: chunk q0 + i
+      const f32x4* h = reinterpret_cast<const f32x4*>(vals[round & 1][mine][lane & 1]);
+      f32x4 x[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) x[i] = h[i];
+      float acc = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_fmaf(x[i][e], x[i][e], acc);
+      const float other = __builtin_bit_cast(
+          float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, acc), 0xB1, 0xF, 0xF, false));
+      const float sum = acc + other;  // first + second on the even lanes
+      for (int i = 0; i < n; ++i) {
+        const float one = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sum), 2 * i));
+        S = (q0 + i == 0) ? one : S + one;  // chunk 0 starts the sum
+      }
+    }
+  }
+  if (tid == 0) s.partials[t] = S;
+}
+
 // partials[t] = chunk statistics of token t added in ascending chunk order.
 // The loads go out sixteen at a time before their sums (a plain loop waited
 // for each load before the next add: 6.0 us for the prefill shard, 4.6 us
@@ -1147,8 +1279,6 @@ const TileShape& choose_tile() {
 // together or apart, and any device, give the same bits.
 constexpr int64_t kSplitMaxRowTiles = 8;
 constexpr int64_t kSplitRowSlices = kMaxSplits;
-constexpr int kSplitBk = 64;
-constexpr int kSplitStages = 4;  // a 256-deep slice has all its loads in flight at once
 
 struct Plan {
   int64_t m_tiles, n_tiles, chunks, ncols;
@@ -1347,6 +1477,7 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
   const auto round8 = [](int64_t v) { return (v + kXcds - 1) / kXcds * kXcds; };
   const int64_t max_wgs = 0x7fffffff - 2 * kXcds;
   int64_t grid = 0;
+  int block = kThreads;
   const char* name = ts.name;
   int lds = ts.lds_bytes;
   const void* gemm = reinterpret_cast<const void*>(ts.fn);
@@ -1358,20 +1489,38 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
     if (tiles * pl.splits > max_wgs) return QKN_ENOTSUP;
     grid = tiles * pl.splits;
     if (half) {
-      gemm = reinterpret_cast<const void*>(qkn_proj_gemm_split<1, kSplitBk, kSplitStages>);
+      // more workgroups than CUs: eight wavefronts each in two-stage rings, up to
+      // three workgroups per CU (64 tokens, weights from HBM: 2560 columns 16.1
+      // against 18.5 us, 5120 columns 26.2 against 27.1); up to one per CU, four
+      // wavefronts with the whole slice in flight (1280 columns 12.0 against 12.8)
+      if (grid > kCus) {
+        gemm = reinterpret_cast<const void*>(qkn_proj_gemm_split<64, 2>);
+        block = kBigThreads;
+      } else {
+        gemm = reinterpret_cast<const void*>(qkn_proj_gemm_decode);
+      }
       name = "proj<64x128,64,dl4,splitk>";
       lds = DlCfg<1, kSplitBk, kSplitStages>::kLdsBytes;
     } else {
-      gemm = reinterpret_cast<const void*>(qkn_proj_gemm_split<2, kSplitBk, kSplitStages>);
+      // Two workgroups per CU on two-stage rings, or one on a four-stage ring:
+      // the former where a second one exists for most CUs (777 tokens, hidden
+      // 4096, 2560 columns: 36.7 against 44.6 us; 1280 columns, one per CU: 31.3
+      // against 26.5) unless the slices are long and more rounds follow (512
+      // tokens, hidden 8192, 5120 columns: 87 against 80 us), and where a slice
+      // is too short to fill four stages (100 tokens, hidden 1024: 9.9 against 10.6).
+      const int nk = (pl.kslice + 63) / 64;
+      const bool two = nk <= 2 || (grid > kCus && (grid <= 2 * kCus || nk <= 4 || (nk <= 8 && p.m_tiles > 1)));
+      gemm = two ? reinterpret_cast<const void*>(qkn_proj_gemm_split<128, 2>)
+                 : reinterpret_cast<const void*>(qkn_proj_gemm_split<128, 4>);
       name = "proj<128x128,64,dl4,splitk>";
-      lds = DlCfg<2, kSplitBk, kSplitStages>::kLdsBytes;
+      lds = BigCfg<128, 128, 4>::kLds;
+      block = kBigThreads;
     }
   } else {
     const int64_t tiles = static_cast<int64_t>(p.m_tiles) * p.n_tiles;
     if (tiles > max_wgs) return QKN_ENOTSUP;
     grid = round8(tiles);
   }
-  int block = kThreads;
   if (!split && g_tile_choice == 0) {
     // the large-tile kernel where it is faster; it reports kernel 1's name,
     // whose results it gives bit for bit (512 threads tell it apart)
@@ -1406,10 +1555,15 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
     int64_t most = 0;  // chunks of the widest segment: one wavefront each, up to kReduceWaves
     for (int i = 0; i < nseg; ++i) most = p.seg[i].nchunks > most ? p.seg[i].nchunks : most;
     const int waves = most < kReduceWaves ? static_cast<int>(most) : kReduceWaves;
-    const void* reduce = pl.splits == 2   ? reinterpret_cast<const void*>(qkn_proj_reduce<2>)
-                         : pl.splits == 4 ? reinterpret_cast<const void*>(qkn_proj_reduce<4>)
-                         : pl.splits == 8 ? reinterpret_cast<const void*>(qkn_proj_reduce<8>)
-                                          : reinterpret_cast<const void*>(qkn_proj_reduce<16>);
+#define QKN_REDUCE(n)                                           \
+  (many ? reinterpret_cast<const void*>(qkn_proj_reduce_many<n>) \
+        : reinterpret_cast<const void*>(qkn_proj_reduce<n>))
+    const bool many = T * nseg > 2 * kCus;
+    const void* reduce = pl.splits == 2   ? QKN_REDUCE(2)
+                         : pl.splits == 4 ? QKN_REDUCE(4)
+                         : pl.splits == 8 ? QKN_REDUCE(8)
+                                          : QKN_REDUCE(16);
+#undef QKN_REDUCE
     if (hipLaunchKernel(reduce, dim3(static_cast<unsigned>(T), static_cast<unsigned>(nseg)),
                         dim3(64 * waves), args, 0, st) != hipSuccess)
       return QKN_EHIP;
