@@ -655,9 +655,9 @@ __device__ __forceinline__ void dl_mainloop(const ProjParams& p, const ProjSegDe
 // port and L2 set the rest. Four wavefronts of 128 x 128 (one per SIMD, so
 // nothing covers a wait) took 155-160 us, loads spread between the LDS reads
 // and raised wave priorities changed nothing.
-template <int TM, int TN, int S_>
+template <int TM, int TN>
 struct BigCfg {
-  static constexpr int S = S_;                               // LDS stages
+  static constexpr int S = 2;                                // LDS stages
   static constexpr int kWr = 2, kWc = 4;                     // wavefronts over the tile's rows and columns
   static constexpr int kWaves = kWr * kWc;
   static constexpr int BK = 64;
@@ -672,11 +672,10 @@ struct BigCfg {
   static constexpr int kLds = (S * kStage > TM * kOutRow * 2) ? S * kStage : TM * kOutRow * 2;
   static_assert(kLoadsA * 1024 * kWaves == kBytesA && kLoadsB * 1024 * kWaves == kBytesB, "whole loads");
   static_assert((kLoadsA == 1 || kLoadsA % 2 == 0) && kLoadsB % 2 == 0, "the slots' swizzle of a load is known");
-  static_assert(S == 2 || S == 4, "the stage loop is unrolled by S");
   static_assert(kLds <= kLdsBytes, "LDS");
 };
 
-constexpr int kBigThreads = 64 * BigCfg<256, 256, 2>::kWaves;
+constexpr int kBigThreads = 64 * BigCfg<256, 256>::kWaves;
 
 __device__ __forceinline__ void load16_to_lds_at(Rsrc r, LdsByte* dst, uint32_t voff, uint32_t soff) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, voff, soff, 0, 0);
@@ -689,11 +688,12 @@ __device__ __forceinline__ bf16x8 lds_frag(LdsByte* at) {
 // Main loop of one tile of TM rows from m0 (rows_a valid) by TN columns from
 // n0 of segment s (rows_b valid), k in [k_lo, k_hi). acc[i][j], lane l: token
 // 16 i + l mod 16, columns 16 j + 4 (l / 16) + r of the wavefront's share.
-template <int TM, int TN, int S>
+template <int TM, int TN>
 __device__ __forceinline__ void big_mainloop(const ProjParams& p, const ProjSegDev& s, unsigned char* lds,
                                              int64_t m0, int n0, int rows_a, int rows_b, int k_lo, int k_hi,
-                                             f32x4 (&acc)[BigCfg<TM, TN, S>::kMi][BigCfg<TM, TN, S>::kNi]) {
-  using C = BigCfg<TM, TN, S>;
+                                             f32x4 (&acc)[BigCfg<TM, TN>::kMi][BigCfg<TM, TN>::kNi]) {
+  using C = BigCfg<TM, TN>;
+  constexpr int S = C::S;
   const int tid = static_cast<int>(threadIdx.x);
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -792,11 +792,6 @@ __device__ __forceinline__ void big_mainloop(const ProjParams& p, const ProjSegD
   for (int kt = 0; kt < nk; kt += S) {  // stages past nk multiply zeros
     QKN_BIG_STAGE(0);
     QKN_BIG_STAGE(1);
-    if constexpr (S == 4) {
-      if (kt + 2 >= nk) break;
-      QKN_BIG_STAGE(2);
-      QKN_BIG_STAGE(3);
-    }
   }
 #undef QKN_BIG_STAGE
 #undef QKN_BIG_MFMA
@@ -805,13 +800,165 @@ __device__ __forceinline__ void big_mainloop(const ProjParams& p, const ProjSegD
   __syncthreads();
 }
 
+// Main loop of a TM x 128 tile with the roles split: wavefronts 0..3 (2 x 2,
+// one per SIMD) multiply, (TM / 2) x 64 each, and 4..7 issue the direct loads,
+// a ring of S stages ahead. A 128 x 128 tile is bound by LDS: eight
+// multiplying wavefronts of 64 x 32 read 96 KB of it per stage of 64 k and the
+// loads fill 32 KB, 1024 cycles at 128 bytes per cycle for 512 of MFMAs; four of
+// 64 x 64 read 64 KB, 768 cycles, and without a partner on their SIMD they keep
+// the MFMAs fed only because they never wait for a load's issue. Measured per
+// stage 0.32 us against 0.41 (1536 tokens x 1280 columns, hidden 4096: 28.5
+// against 33.8 us). Fragments are double-buffered by halves of 32 k as above;
+// one barrier per stage: the multiplying wavefronts then have the stage's
+// second half in registers, the loading ones have waited for the next stage.
+template <int TM, int S_>
+struct DuoCfg {
+  static constexpr int S = S_;
+  static constexpr int kBytesA = TM * 128, kBytesB = 128 * 128, kStage = kBytesA + kBytesB;
+  static constexpr int kLoadsA = kBytesA / 4096, kLoadsB = kBytesB / 4096, kLoads = kLoadsA + kLoadsB;
+  static constexpr int kMi = TM / 32, kNi = 4;
+  static constexpr int kOutRow = 128 + 8;
+  static constexpr int kLds = (S * kStage > TM * kOutRow * 2) ? S * kStage : TM * kOutRow * 2;
+  static_assert(kLoadsA % 2 == 0, "a wavefront's loads start at a multiple of 16 rows");
+  static_assert(kLds <= kLdsBytes, "LDS");
+};
+
+template <int TM, int S>
+__device__ __forceinline__ void duo_mainloop(const ProjParams& p, const ProjSegDev& s, unsigned char* lds,
+                                             int64_t m0, int n0, int rows_a, int rows_b, int k_lo, int k_hi,
+                                             f32x4 (&acc)[DuoCfg<TM, S>::kMi][4]) {
+  using C = DuoCfg<TM, S>;
+  const int tid = static_cast<int>(threadIdx.x);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nk = (k_hi - k_lo + 63) / 64;
+  const int rounds = (nk + S - 1) / S * S;  // stages past nk multiply zeros
+  if (wave >= 4) {
+    const int w = wave - 4;
+    const uint32_t a_bytes = static_cast<uint32_t>(rows_a * p.ldx * 2);
+    const uint32_t b_bytes = static_cast<uint32_t>(rows_b * s.ldw * 2);
+    const Rsrc ra = make_rsrc(p.x + m0 * p.ldx, a_bytes);
+    const Rsrc rb = make_rsrc(s.w + static_cast<int64_t>(n0) * s.ldw, b_bytes);
+    const int kv[2] = {((lane & 7) ^ (lane >> 4)) * 8, (((lane & 7) ^ (lane >> 4)) * 8) ^ 32};
+    uint32_t va[2], vb[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      va[i] = static_cast<uint32_t>(((w * C::kLoadsA + i) * 8 + (lane >> 3)) * p.ldx * 2) + kv[i] * 2;
+      vb[i] = static_cast<uint32_t>(((w * C::kLoadsB + i) * 8 + (lane >> 3)) * s.ldw * 2) + kv[i] * 2;
+    }
+    const uint32_t step_a = static_cast<uint32_t>(32 * p.ldx), step_b = static_cast<uint32_t>(32 * s.ldw);
+    auto issue = [=](int slot, int kt) __attribute__((always_inline)) {
+      const bool live = kt < nk;
+      const int k0 = live ? k_lo + kt * 64 : 0;
+      const bool ok[2] = {live && k0 + kv[0] < k_hi, live && k0 + kv[1] < k_hi};
+      LdsByte* base = (LdsByte*)(lds + slot * C::kStage);
+#pragma unroll
+      for (int n = 0; n < C::kLoadsA; ++n)
+        load16_to_lds_at(ra, base + (w * C::kLoadsA + n) * 1024,
+                         ok[n & 1] ? va[n & 1] + (n >> 1) * step_a : a_bytes, k0 * 2);
+#pragma unroll
+      for (int n = 0; n < C::kLoadsB; ++n)
+        load16_to_lds_at(rb, base + C::kBytesA + (w * C::kLoadsB + n) * 1024,
+                         ok[n & 1] ? vb[n & 1] + (n >> 1) * step_b : b_bytes, k0 * 2);
+    };
+#pragma unroll
+    for (int q = 0; q < S; ++q) issue(q, q);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 1) * C::kLoads));
+    __builtin_amdgcn_s_barrier();
+    for (int kt = 0; kt < rounds; kt += S) {
+#pragma unroll
+      for (int q = 0; q < S; ++q) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * C::kLoads));
+        __builtin_amdgcn_s_barrier();
+        issue(q, kt + q + S);
+      }
+    }
+  } else {
+    const int wm = wave >> 1, wn = wave & 1;
+    const int fr = lane & 15;
+    const int fslot = ((lane >> 4) ^ (fr >> 1)) * 16;
+    LdsByte* fa[S][2];
+    LdsByte* fb[S][2];
+#pragma unroll
+    for (int q = 0; q < S; ++q)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        fa[q][h] = (LdsByte*)lds + q * C::kStage + (wm * (TM / 2) + fr) * 128 + (fslot ^ (64 * h));
+        fb[q][h] = (LdsByte*)lds + q * C::kStage + C::kBytesA + (wn * 64 + fr) * 128 + (fslot ^ (64 * h));
+        asm volatile("" : "+v"(fa[q][h]), "+v"(fb[q][h]));
+      }
+#pragma unroll
+    for (int i = 0; i < C::kMi; ++i)
+#pragma unroll
+      for (int j = 0; j < C::kNi; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    bf16x8 A[2][C::kMi], B[2][C::kNi];
+    __builtin_amdgcn_s_barrier();
+#define QKN_DUO_READ(set, slot, half)                                                                    \
+  _Pragma("unroll") for (int j = 0; j < C::kNi; ++j) B[set][j] = lds_frag(fb[slot][half] + j * 2048);    \
+  _Pragma("unroll") for (int i = 0; i < C::kMi; ++i) A[set][i] = lds_frag(fa[slot][half] + i * 2048)
+#define QKN_DUO_MFMA(set)                                                                                \
+  _Pragma("unroll") for (int i = 0; i < C::kMi; ++i)                                                     \
+      _Pragma("unroll") for (int j = 0; j < C::kNi; ++j) acc[i][j] =                                     \
+          __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[set][j], A[set][i], acc[i][j], 0, 0, 0);             \
+  _Pragma("unroll") for (int g = 0; g < C::kMi + C::kNi; ++g) {                                          \
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                   \
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                                   \
+  }                                                                                                      \
+  __builtin_amdgcn_sched_group_barrier(0x008, C::kMi * C::kNi, 0);                                       \
+  __builtin_amdgcn_sched_barrier(0)
+    QKN_DUO_READ(0, 0, 0);
+    for (int kt = 0; kt < rounds; kt += S) {
+#pragma unroll
+      for (int q = 0; q < S; ++q) {
+        QKN_DUO_READ(1, q, 1);
+        QKN_DUO_MFMA(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        QKN_DUO_READ(0, (q + 1) % S, 0);
+        QKN_DUO_MFMA(1);
+      }
+    }
+#undef QKN_DUO_MFMA
+#undef QKN_DUO_READ
+  }
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  __syncthreads();
+}
+
+// One such tile with its epilogue.
+template <int TM, int S>
+__device__ __forceinline__ void duo_tile(const ProjParams& p, const ProjSegDev& s, unsigned char* lds,
+                                         int64_t m0, int n0, int rows_a, int rows_b) {
+  using C = DuoCfg<TM, S>;
+  f32x4 acc[C::kMi][4];
+  duo_mainloop<TM, S>(p, s, lds, m0, n0, rows_a, rows_b, 0, p.hidden, acc);
+  const int tid = static_cast<int>(threadIdx.x);
+  const int lane = tid & 63, wave = tid >> 6;
+  uint16_t* out = reinterpret_cast<uint16_t*>(lds);  // [TM][kOutRow]
+  if (wave < 4) {
+#pragma unroll
+    for (int i = 0; i < C::kMi; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int row = (wave >> 1) * (TM / 2) + i * 16 + (lane & 15);
+        const int col = (wave & 1) * 64 + j * 16 + 4 * (lane >> 4);
+        const uint64_t v = (static_cast<uint64_t>(pack_bf16x2(acc[i][j][2], acc[i][j][3])) << 32) |
+                           pack_bf16x2(acc[i][j][0], acc[i][j][1]);
+        *reinterpret_cast<uint64_t*>(out + row * C::kOutRow + col) = v;
+      }
+  }
+  __syncthreads();
+  epilogue_staged<TM, 128, C::kOutRow, kBigThreads>(p, s, out, m0, n0, rows_a, rows_b);
+}
+
 // One tile with its epilogue.
-template <int TM, int TN, int S>
+template <int TM, int TN>
 __device__ __forceinline__ void big_tile(const ProjParams& p, const ProjSegDev& s, unsigned char* lds,
                                          int64_t m0, int n0, int rows_a, int rows_b) {
-  using C = BigCfg<TM, TN, S>;
+  using C = BigCfg<TM, TN>;
   f32x4 acc[C::kMi][C::kNi];
-  big_mainloop<TM, TN, S>(p, s, lds, m0, n0, rows_a, rows_b, 0, p.hidden, acc);
+  big_mainloop<TM, TN>(p, s, lds, m0, n0, rows_a, rows_b, 0, p.hidden, acc);
   const int tid = static_cast<int>(threadIdx.x);
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave / C::kWc, wn = wave % C::kWc;
@@ -837,10 +984,10 @@ __device__ __forceinline__ int xcd_run(int b, int n) {
   return x * per + (x < extra ? x : extra) + b / kXcds;
 }
 
-// The work list of BigGrid, one tile per workgroup. The small tiles run the
-// same loop with 64 x 32 per wavefront and a ring of four stages.
-constexpr int kBigLds = BigCfg<256, 256, 2>::kLds;
-static_assert(BigCfg<128, 128, 4>::kLds <= kBigLds, "LDS of the small tiles");
+// The work list of BigGrid, one tile per workgroup; the small tiles run the
+// role-split loop on a ring of four stages.
+constexpr int kBigLds = BigCfg<256, 256>::kLds;
+static_assert(DuoCfg<128, 4>::kLds <= kBigLds, "LDS of the small tiles");
 __global__ __launch_bounds__(kBigThreads, 2) void qkn_proj_gemm_big(const ProjParams p) {
   __shared__ __align__(1024) unsigned char lds[kBigLds];
   const BigGrid& g = p.big;
@@ -891,11 +1038,10 @@ __global__ __launch_bounds__(kBigThreads, 2) void qkn_proj_gemm_big(const ProjPa
   const int right = s.d - col;
   if (left <= 0 || right <= 0) return;  // a quarter or a strip tile outside the output
   if (!small)
-    big_tile<256, 256, 2>(p, s, lds, row, col, static_cast<int>(left < 256 ? left : 256),
+    big_tile<256, 256>(p, s, lds, row, col, static_cast<int>(left < 256 ? left : 256),
                           right < 256 ? right : 256);
   else
-    big_tile<128, 128, 4>(p, s, lds, row, col, static_cast<int>(left < 128 ? left : 128),
-                          right < 128 ? right : 128);
+    duo_tile<128, 4>(p, s, lds, row, col, static_cast<int>(left < 128 ? left : 128), right < 128 ? right : 128);
 }
 
 // The segment, origin and valid extent of output tile (row tile mt of height
@@ -966,17 +1112,19 @@ __device__ __forceinline__ void acc_to_lds(const f32x4 (&acc)[C::kMi][C::kNi], f
 }
 
 // Split k: a workgroup takes one k-slice of one TM x 128 tile with the
-// large-tile kernel's loop and stores its fp32 sums into the slice array
-// instead of running the epilogue. Bound by LDS like the small tiles there
-// (0.41 us per stage of 64 k) plus 6 us of first loads, stores and launch.
-// Against four wavefronts of 64 x 64 without fragments ahead and with each
-// XCD's workgroups spread over all tiles (so that every XCD's L2 fetched
-// nearly all of x and W): 777 tokens, hidden 5120, 1536 columns 33.4 -> 24.8 us.
+// role-split loop on four stages, or the eight-wavefront one on two (two or
+// three workgroups per CU), and stores its fp32 sums into the slice array
+// instead of running the epilogue. Bound by LDS like the small whole tiles
+// (0.32 us per stage of 64 k) plus 6 us of first loads, stores and launch.
+// Before, four wavefronts of 64 x 64 without fragments ahead, and with each
+// XCD's workgroups spread over all tiles so that every XCD's L2 fetched nearly
+// all of x and W: 512 tokens, hidden 4096, 1536 columns 22.4 -> 17.5 us a call.
 template <int TM, int S>
 __global__ __launch_bounds__(kBigThreads, S == 2 ? 4 : 2) void qkn_proj_gemm_split(const ProjParams p) {
-  using C = BigCfg<TM, 128, S>;
+  constexpr bool kDuo = S == 4;
+  constexpr int kStages = kDuo ? DuoCfg<TM, S>::kLds : BigCfg<TM, 128>::kLds;
   constexpr int kRow = 128 + 4;  // fp32 per row of the tile staged for the stores
-  constexpr int kLds = C::kLds > TM * kRow * 4 ? C::kLds : TM * kRow * 4;
+  constexpr int kLds = kStages > TM * kRow * 4 ? kStages : TM * kRow * 4;
   __shared__ __align__(1024) unsigned char lds[kLds];
   const int b = xcd_run(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
   // slice-major runs: an XCD's workgroups share the slice's columns of x and W
@@ -993,13 +1141,20 @@ __global__ __launch_bounds__(kBigThreads, S == 2 ? 4 : 2) void qkn_proj_gemm_spl
   const int n0 = (nt - s.tile0) * 128;
   const int rows_a = static_cast<int>((p.T - m0 < TM) ? p.T - m0 : TM);
   const int rows_b = (s.d - n0 < 128) ? s.d - n0 : 128;
-  f32x4 acc[C::kMi][C::kNi];
-  big_mainloop<TM, 128, S>(p, s, lds, m0, n0, rows_a, rows_b, k_lo, k_hi, acc);
-  // through LDS, to write rows out in 16-byte vectors of adjacent lanes
   const int tid = static_cast<int>(threadIdx.x);
   const int wave = tid >> 6;
-  float* tile = reinterpret_cast<float*>(lds);
-  acc_to_lds<C>(acc, tile, kRow, (wave / C::kWc) * (TM / C::kWr), (wave % C::kWc) * 32, tid & 63);
+  float* tile = reinterpret_cast<float*>(lds);  // to write rows out in 16-byte vectors of adjacent lanes
+  if constexpr (kDuo) {
+    using C = DuoCfg<TM, S>;
+    f32x4 acc[C::kMi][C::kNi];
+    duo_mainloop<TM, S>(p, s, lds, m0, n0, rows_a, rows_b, k_lo, k_hi, acc);
+    if (wave < 4) acc_to_lds<C>(acc, tile, kRow, (wave >> 1) * (TM / 2), (wave & 1) * 64, tid & 63);
+  } else {
+    using C = BigCfg<TM, 128>;
+    f32x4 acc[C::kMi][C::kNi];
+    big_mainloop<TM, 128>(p, s, lds, m0, n0, rows_a, rows_b, k_lo, k_hi, acc);
+    acc_to_lds<C>(acc, tile, kRow, (wave / C::kWc) * (TM / C::kWr), (wave % C::kWc) * 32, tid & 63);
+  }
   __syncthreads();
   // a row's valid columns are a multiple of 8 (d_local is), and its first
   // column's offset in the slice array is a multiple of 8 floats, so every
@@ -1314,19 +1469,32 @@ Plan plan_of(int64_t T, int64_t hidden, const qkn_proj_seg* segs, int nseg) {
   return pl;
 }
 
-// Costs of one round over the CUs in hundredths of a round of 256 x 256 tiles
-// (one per CU): 128 x 128 tiles of the large-tile kernel (one per CU) 35,
-// 128 x 128 tiles of the two-stage kernel (two per CU) 60. Measured at hidden
-// 4096: rounds of 98, 31-36 and 57-61 us; so up to 256 small tiles the
-// large-tile kernel's are 1.4-1.6 times as fast (33 against 51 us for 1536
-// tokens x 1280 columns), for 257 to 512 the two-stage kernel's two per CU win
-// (57 against 62 us), and beyond, large tiles are 1.25-1.35 times as fast.
-constexpr int kRoundBig = 100, kRoundSmall = 35, kRoundOld = 60;
+// Time of `rounds` rounds over the CUs with nk stages of 64 k, in hundredths
+// of a microsecond: 256 x 256 tiles (one per CU), 128 x 128 tiles of the
+// large-tile kernel (one per CU), 128 x 128 tiles of the two-stage kernel (two
+// per CU). Fitted to whole calls at 1025 to 12000 tokens, 640 to 5120 columns,
+// hidden 1024 and 4096. So up to 256 small tiles take the role-split loop
+// (1536 tokens x 1280 columns, hidden 4096: 28.8 against 51.2 us), 257 to 512
+// take it from hidden 3072 or so (4096 tokens x 1536 columns: hidden 4096 55.3
+// against 60.0 us, hidden 1024 24.5 against 24.1), and larger launches take
+// large tiles (8192 tokens x 5120 columns: hidden 4096 269 against 349 us,
+// hidden 1024 93 against 102).
+// Where strips of small tiles run beside large ones, neighbours share fewer
+// rows of x (8192 tokens, 640 + 384 columns, hidden 4096, all small: 69.4
+// against 66.9 us in the two-stage kernel); several rounds of few stages lose
+// to its two workgroups per CU (8192 tokens, 2560 columns: hidden 256 26.0
+// against 22.6 us, hidden 512 35.9 against 32.3).
+int64_t time_big(int64_t rounds, int64_t nk) { return rounds ? 900 + rounds * (50 + 118 * nk) : 0; }
+int64_t time_small(int64_t rounds, int64_t nk, bool strips) {
+  return rounds * ((rounds > 1 ? 1050 : 750) + (strips ? 45 : 33) * nk);
+}
+constexpr int64_t kShallow = 16;  // stages below which only single rounds take the large-tile kernel
+int64_t time_two_stage(int64_t rounds, int64_t nk) { return 800 + 105 * nk * rounds; }
+int64_t rounds_of(int64_t tiles, int64_t per_round) { return (tiles + per_round - 1) / per_round; }
 
 // Large tiles cover every 256-block that is at least half full. Those of an
 // incomplete last round are computed as quarters where that takes less time.
-BigGrid big_grid(int64_t T, const qkn_proj_seg* segs, int nseg, int* cost) {
-  const auto rounds = [](int64_t n) { return static_cast<int>((n + kCus - 1) / kCus); };
+BigGrid big_grid(int64_t T, int64_t nk, const qkn_proj_seg* segs, int nseg, int64_t* time) {
   BigGrid g{};
   const int64_t rest = T % 256;
   g.rows = static_cast<int32_t>(T / 256 + (rest > 128 ? 1 : 0));
@@ -1341,14 +1509,16 @@ BigGrid big_grid(int64_t T, const qkn_proj_seg* segs, int nseg, int* cost) {
   g.bigs = g.rows * (g.cols[0] + g.cols[1]);
   const int64_t other = g.strip_tiles + (rest > 0 && rest <= 128 ? n128 : 0);
   const int rem = g.bigs % kCus;
-  const int full = kRoundBig * (g.bigs / kCus);
   // CUs without a large tile in its last round take two small ones meanwhile
   const int64_t beside = rem ? 2 * (kCus - rem) : 0;
-  const int as_big = full + (rem ? kRoundBig : 0) + kRoundSmall * rounds(other > beside ? other - beside : 0);
-  const int as_small = full + kRoundSmall * rounds(int64_t{4} * rem + other);
+  const int64_t after = other > beside ? other - beside : 0;
+  const bool strips = g.strip_tiles > 0;
+  const int64_t as_big = time_big(rounds_of(g.bigs, kCus), nk) + time_small(rounds_of(after, kCus), nk, strips);
+  const int64_t as_small =
+      time_big(g.bigs / kCus, nk) + time_small(rounds_of(int64_t{4} * rem + other, kCus), nk, strips);
   g.whole = g.bigs - (as_small < as_big ? rem : 0);
   g.smalls = static_cast<int32_t>(int64_t{4} * (g.bigs - g.whole) + other);
-  *cost = as_small < as_big ? as_small : as_big;
+  *time = as_small < as_big ? as_small : as_big;
   return g;
 }
 
@@ -1502,18 +1672,23 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
       name = "proj<64x128,64,dl4,splitk>";
       lds = DlCfg<1, kSplitBk, kSplitStages>::kLdsBytes;
     } else {
-      // Two workgroups per CU on two-stage rings, or one on a four-stage ring:
-      // the former where a second one exists for most CUs (777 tokens, hidden
-      // 4096, 2560 columns: 36.7 against 44.6 us; 1280 columns, one per CU: 31.3
-      // against 26.5) unless the slices are long and more rounds follow (512
-      // tokens, hidden 8192, 5120 columns: 87 against 80 us), and where a slice
-      // is too short to fill four stages (100 tokens, hidden 1024: 9.9 against 10.6).
+      // Two workgroups per CU of eight multiplying wavefronts on two-stage
+      // rings, or one on a four-stage ring with the roles split. Measured at
+      // hidden 4096 unless said, role-split time first: up to one workgroup per CU the latter (512 tokens, 1536 columns 17.5
+      // against 21.4 us) unless a slice has two stages or fewer (hidden 1024, 100
+      // tokens, 768 columns 9.5 against 8.6); up to two per CU the former (384
+      // tokens, 5120 columns 38.8 against 35.9) unless the second round is small
+      // and the slices long (777 tokens, hidden 8192, 2560 columns 59.5 against
+      // 70.9); beyond, the former for short slices (128 tokens, 5120 columns 34.6
+      // against 32.9; 512 tokens 54.2 against 56.0).
       const int nk = (pl.kslice + 63) / 64;
-      const bool two = nk <= 2 || (grid > kCus && (grid <= 2 * kCus || nk <= 4 || (nk <= 8 && p.m_tiles > 1)));
+      const bool two = grid <= kCus       ? nk <= 2
+                       : grid <= 2 * kCus ? nk < 32 || 2 * grid >= 3 * kCus
+                                          : nk <= 4 || (nk <= 8 && p.m_tiles > 1);
       gemm = two ? reinterpret_cast<const void*>(qkn_proj_gemm_split<128, 2>)
                  : reinterpret_cast<const void*>(qkn_proj_gemm_split<128, 4>);
       name = "proj<128x128,64,dl4,splitk>";
-      lds = BigCfg<128, 128, 4>::kLds;
+      lds = DuoCfg<128, 4>::kLds;
       block = kBigThreads;
     }
   } else {
@@ -1524,10 +1699,11 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
   if (!split && g_tile_choice == 0) {
     // the large-tile kernel where it is faster; it reports kernel 1's name,
     // whose results it gives bit for bit (512 threads tell it apart)
-    int cost = 0;
-    p.big = big_grid(T, segs, nseg, &cost);
+    const int64_t nk = (hidden + 63) / 64;
+    int64_t time = 0;
+    p.big = big_grid(T, nk, segs, nseg, &time);
     const int64_t tiles = static_cast<int64_t>(p.m_tiles) * p.n_tiles;
-    if (cost < kRoundOld * ((tiles + 2 * kCus - 1) / (2 * kCus))) {
+    if (time < time_two_stage(rounds_of(tiles, 2 * kCus), nk) && (nk >= kShallow || tiles <= kCus)) {
       gemm = reinterpret_cast<const void*>(qkn_proj_gemm_big);
       grid = static_cast<int64_t>(p.big.whole) + p.big.smalls;
       block = kBigThreads;

@@ -48,9 +48,10 @@ CASES = [
     (1280, 64, 128, 120, 0),        # one k-stage; strips only
     (1300, 1096, 1280, 256, 16),
     (1279, 320, 520, 384, 0),       # k-stages in an incomplete ring
-    (2560, 136, 4096, 1032, 8),     # large tiles only, one incomplete round
-    (8200, 192, 2048, 512, 0),      # a round of large tiles, the rest quartered, a row below
-    (8192, 128, 2176, 392, 24),     # the same with strips
+    (2560, 1160, 4096, 1032, 8),    # large tiles only, one incomplete round
+    (8152, 1096, 2048, 512, 0),     # a round of large tiles, the rest quartered
+    (8200, 2048, 2048, 512, 0),     # the same with a row below
+    (8192, 4096, 2176, 392, 24),    # the same with strips
     (5000, 1024, 4096, 1024, 0),
 ]
 
