@@ -351,7 +351,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # no longer describe the kernel
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2608_09160_amd", "csrc", f)
                   for f in ("qkn_kernels.h", "qkn_kern_rows.hip", "qkn_kern_wait.hip",
-                            "qkn_kern_wait8.hip", "qkn_kern_misc.hip", "qkn.hip")]
+                            "qkn_kern_wait8.hip", "qkn_kern_any.hip", "qkn_kern_once.hip",
+                            "qkn_kern_misc.hip", "qkn.hip")]
 
 
 def source_sha256() -> str:

@@ -20,7 +20,7 @@ ROOT = os.path.dirname(PKG_DIR)
 # qkn_kernels.h), split so that the units compile in parallel.
 SOURCES = [os.path.join(PKG_DIR, "csrc", name)
            for name in ("qkn.hip", "qkn_kern_rows.hip", "qkn_kern_wait.hip", "qkn_kern_wait8.hip",
-                        "qkn_kern_any.hip", "qkn_kern_misc.hip", "qkn_proj.hip", "qkn_calib.hip")]
+                        "qkn_kern_any.hip", "qkn_kern_once.hip", "qkn_kern_misc.hip", "qkn_proj.hip", "qkn_calib.hip")]
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG_DIR, "libqkn.so")
 ARCH = "gfx950"

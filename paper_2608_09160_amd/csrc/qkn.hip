@@ -468,6 +468,18 @@ int launch(const HSeg* segs, int nseg, int tp, int rank, int64_t T, float eps, i
   if (grid > 0x7fffffff) grid = 0x7fffffff;
   if ((fast || any) && g_opt_token_blocks) kp.tok_chunk = (T + grid * wpb - 1) / (grid * wpb);
 
+  // A wavefront for every token: the kernels without a loop (per graph node, 256
+  // tokens of 640 + 128 columns 2.9 against 3.2 us, 3000 of 256 + 128 3.9
+  // against 4.5; the most one round takes, 1536 tokens, of 4096 + 1024 columns
+  // 6.9 against 7.8, of 2048 + 512 5.2 against 5.1). Longer launches keep the
+  // loop: with the same argument loads ahead of it, 8192 tokens of 2048 + 512
+  // columns took 15.9 against 15.8 us in bf16 and 10.4 against 10.0 in fp8.
+  if (fast && !waits && block == kWave && grid == T && !g_opt_prefetch && !g_opt_token_blocks) {
+    if (mode == kFused) fn = reinterpret_cast<const void*>(kOnceFusedTable[fmt][idx[0]][i1]);
+    else if (mode == kApply) fn = reinterpret_cast<const void*>(kOnceApplyTable[fmt][idx[0]]);
+    else fn = reinterpret_cast<const void*>(kOncePartialTable[fmt][idx[0]]);
+  }
+
   hipError_t err;
   if (fast || any || wide) {
     void* args[] = {&kp};
