@@ -125,8 +125,42 @@ struct ProjParams {
   int32_t kslice;        // k per slice, a multiple of the stage k
   float* part;
   int32_t ncols;         // columns of both segments
+  int32_t reduce_waves;  // wavefronts per workgroup of the reduction
   BigGrid big;           // large-tile kernel
 };
+
+// Segment `second` of the launch, its fields chosen by value: an index would
+// put each field's load behind the choice, a round trip to memory every time.
+__device__ __forceinline__ ProjSegDev pick_seg(const ProjParams& p, bool second) {
+  const ProjSegDev &a = p.seg[0], &b = p.seg[1];
+  ProjSegDev s;
+  s.w = second ? b.w : a.w;
+  s.y = second ? b.y : a.y;
+  s.tile_partials = second ? b.tile_partials : a.tile_partials;
+  s.partials = second ? b.partials : a.partials;
+  s.ldw = second ? b.ldw : a.ldw;
+  s.ldy = second ? b.ldy : a.ldy;
+  s.d = second ? b.d : a.d;
+  s.tile0 = second ? b.tile0 : a.tile0;
+  s.nchunks = second ? b.nchunks : a.nchunks;
+  s.col0 = second ? b.col0 : a.col0;
+  return s;
+}
+
+// Asks for all arguments of a short split-k launch at once (left to itself the
+// compiler loads each where it is used: four or five round trips in a row
+// before the first load of x or of a slice).
+__device__ __forceinline__ void want_gemm_params(const ProjParams& p) {
+  asm volatile("" ::"s"(p.x), "s"(p.ldx), "s"(p.T), "s"(p.hidden), "s"(p.m_tiles), "s"(p.n_tiles), "s"(p.nseg),
+               "s"(p.splits), "s"(p.kslice), "s"(p.part), "s"(p.ncols), "s"(p.seg[0].w), "s"(p.seg[0].ldw),
+               "s"(p.seg[0].d), "s"(p.seg[0].tile0), "s"(p.seg[0].col0), "s"(p.seg[1].w), "s"(p.seg[1].ldw),
+               "s"(p.seg[1].d), "s"(p.seg[1].tile0), "s"(p.seg[1].col0));
+}
+__device__ __forceinline__ void want_reduce_params(const ProjParams& p) {
+  asm volatile("" ::"s"(p.T), "s"(p.part), "s"(p.ncols), "s"(p.reduce_waves), "s"(p.seg[0].y), "s"(p.seg[0].partials),
+               "s"(p.seg[0].ldy), "s"(p.seg[0].d), "s"(p.seg[0].nchunks), "s"(p.seg[0].col0), "s"(p.seg[1].y),
+               "s"(p.seg[1].partials), "s"(p.seg[1].ldy), "s"(p.seg[1].d), "s"(p.seg[1].nchunks), "s"(p.seg[1].col0));
+}
 
 __device__ __forceinline__ Rsrc make_rsrc(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), static_cast<short>(0),
@@ -1176,14 +1210,21 @@ __global__ __launch_bounds__(kThreads) void qkn_proj_gemm_decode(const ProjParam
   constexpr int MI = 16;  // 16 x 16 x 32 MFMAs (same bits as 32 x 32 x 16, 1-2 % faster here)
   using C = DlCfg<WMB, BK, S>;
   __shared__ __align__(1024) unsigned char lds[C::kLdsBytes];
+  want_gemm_params(p);
   const int b = static_cast<int>(blockIdx.x);
   int mt, nt;
   if (!tile_from(b / p.splits, p.m_tiles, p, mt, nt)) return;
   const int ks = b % p.splits;
   const int k_lo = ks * p.kslice;
   const int k_hi = (k_lo + p.kslice < p.hidden) ? k_lo + p.kslice : p.hidden;
-  const TileAt t = tile_at<WMB>(p, 0, mt, nt);
-  const ProjSegDev& s = p.seg[t.si];
+  mt = __builtin_amdgcn_readfirstlane(mt);
+  nt = __builtin_amdgcn_readfirstlane(nt);
+  const ProjSegDev s = pick_seg(p, p.nseg == 2 && nt >= p.seg[1].tile0);
+  TileAt t;
+  t.m0 = static_cast<int64_t>(mt) * 64;
+  t.n0 = (nt - s.tile0) * 128;
+  t.rows_a = static_cast<int>((p.T - t.m0 < 64) ? p.T - t.m0 : 64);
+  t.rows_b = (s.d - t.n0 < 128) ? s.d - t.n0 : 128;
   using A = AccOf<MI, WMB>;
   typename A::T acc;
   dl_mainloop<MI, WMB, BK, S>(p, s, lds, t.m0, t.n0, t.rows_a, t.rows_b, k_lo, k_hi, acc);
@@ -1234,20 +1275,24 @@ __global__ __launch_bounds__(kThreads) void qkn_proj_gemm_decode(const ProjParam
 // columns' k-slice sums in ascending slice order and rounds them once to bf16
 // (y); the chunk's statistic follows the tile epilogue's tree (two ascending
 // FMA chains over the chunk's halves, first + second); after a barrier the
-// chunk statistics of each segment are added in ascending chunk order.
+// first wavefront adds the segment's chunk statistics in ascending chunk order.
+// Bound by its chain of latencies: arguments, slices, LDS, FMAs. 16 layers of 64
+// tokens, hidden 4096, 1024 + 256 columns (projection and norm): arguments
+// asked for at once here and in the slices' kernel, a chunk's LDS reads ahead of
+// its chain, and statistics a lane each, 253.5 -> 247.9 us.
 constexpr int kMaxSplitChunks = 2048;  // 128-column chunks of both segments
 constexpr int kMaxSplits = 16;         // slices: (row tiles) x (slices) <= 16
 constexpr int kReduceWaves = 16;
 template <int SPLITS>
 __global__ __launch_bounds__(64 * kReduceWaves) void qkn_proj_reduce(const ProjParams p) {
-  __shared__ float vals[kReduceWaves][kChunkN];
+  __shared__ __align__(16) float vals[kReduceWaves][kChunkN];
   __shared__ float chunk_sum[kMaxSplitChunks];
+  want_reduce_params(p);
   const int64_t t = blockIdx.x;
-  const int si = static_cast<int>(blockIdx.y);
-  const ProjSegDev& s = p.seg[si];
+  const ProjSegDev s = pick_seg(p, blockIdx.y != 0);
   const int tid = static_cast<int>(threadIdx.x);
   const int lane = tid & 63, wave = tid >> 6;
-  const int waves = static_cast<int>(blockDim.x) >> 6;
+  const int waves = p.reduce_waves;
   const int64_t slice = p.T * p.ncols;
   float* v = vals[wave];
   for (int q = wave; q < s.nchunks; q += waves) {
@@ -1276,10 +1321,15 @@ __global__ __launch_bounds__(64 * kReduceWaves) void qkn_proj_reduce(const ProjP
     // trip count differs between wavefronts)
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    const float* h = v + (lane & 1) * 64;
+    const f32x4* h = reinterpret_cast<const f32x4*>(v + (lane & 1) * 64);
+    f32x4 x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = h[i];
     float acc_s = 0.0f;
-#pragma unroll 16
-    for (int i = 0; i < 64; ++i) acc_s = __builtin_fmaf(h[i], h[i], acc_s);
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc_s = __builtin_fmaf(x[i][e], x[i][e], acc_s);
     const float other = __builtin_bit_cast(
         float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, acc_s), 0xB1, 0xF, 0xF, false));
     if (lane == 0) chunk_sum[q] = acc_s + other;
@@ -1287,10 +1337,18 @@ __global__ __launch_bounds__(64 * kReduceWaves) void qkn_proj_reduce(const ProjP
     __builtin_amdgcn_wave_barrier();  // the row is read before the next chunk overwrites it
   }
   __syncthreads();
-  if (tid == 0) {
-    float S = chunk_sum[0];
-    for (int n = 1; n < s.nchunks; ++n) S = S + chunk_sum[n];
-    s.partials[t] = S;
+  if (wave == 0) {
+    // a lane per chunk; lanes past the last hold -0, which adds nothing, so
+    // whole groups of four are added
+    float S = -0.0f;
+    for (int n0 = 0; n0 < s.nchunks; n0 += 64) {
+      const int n = s.nchunks - n0 < 64 ? s.nchunks - n0 : 64;
+      const int mine = __builtin_bit_cast(int, lane < n ? chunk_sum[n0 + lane] : -0.0f);
+      for (int i = 0; i < n; i += 4)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) S = S + __builtin_bit_cast(float, __builtin_amdgcn_readlane(mine, i + k));
+    }
+    if (lane == 0) s.partials[t] = S;
   }
 }
 
@@ -1306,12 +1364,12 @@ constexpr int kHalf = kChunkN / 2 + 4;  // floats per staged half chunk
 template <int SPLITS>
 __global__ __launch_bounds__(64 * kReduceWaves) void qkn_proj_reduce_many(const ProjParams p) {
   __shared__ __align__(16) float vals[2][kReduceWaves][2][kHalf];
+  want_reduce_params(p);
   const int64_t t = blockIdx.x;
-  const int si = static_cast<int>(blockIdx.y);
-  const ProjSegDev& s = p.seg[si];
+  const ProjSegDev s = pick_seg(p, blockIdx.y != 0);
   const int tid = static_cast<int>(threadIdx.x);
   const int lane = tid & 63, wave = tid >> 6;
-  const int waves = static_cast<int>(blockDim.x) >> 6;
+  const int waves = p.reduce_waves;
   const int64_t slice = p.T * p.ncols;
   float S = 0.0f;
   for (int q0 = 0, round = 0; q0 < s.nchunks; q0 += waves, ++round) {
@@ -1674,13 +1732,14 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
     } else {
       // Two workgroups per CU of eight multiplying wavefronts on two-stage
       // rings, or one on a four-stage ring with the roles split. Measured at
-      // hidden 4096 unless said, role-split time first: up to one workgroup per CU the latter (512 tokens, 1536 columns 17.5
-      // against 21.4 us) unless a slice has two stages or fewer (hidden 1024, 100
-      // tokens, 768 columns 9.5 against 8.6); up to two per CU the former (384
-      // tokens, 5120 columns 38.8 against 35.9) unless the second round is small
-      // and the slices long (777 tokens, hidden 8192, 2560 columns 59.5 against
-      // 70.9); beyond, the former for short slices (128 tokens, 5120 columns 34.6
-      // against 32.9; 512 tokens 54.2 against 56.0).
+      // hidden 4096 unless said, role-split time first: up to one workgroup per
+      // CU the latter (512 tokens, 1536 columns 17.5 against 21.4 us) unless a
+      // slice has two stages or fewer (hidden 1024, 100 tokens, 768 columns 9.5
+      // against 8.6); up to two per CU the former (384 tokens, 5120 columns 38.8
+      // against 35.9) unless the second round is small and the slices long (777
+      // tokens, hidden 8192, 2560 columns 59.5 against 70.9); beyond, the former
+      // for short slices (128 tokens, 5120 columns 34.6 against 32.9; 512 tokens
+      // 54.2 against 56.0).
       const int nk = (pl.kslice + 63) / 64;
       const bool two = grid <= kCus       ? nk <= 2
                        : grid <= 2 * kCus ? nk < 32 || 2 * grid >= 3 * kCus
@@ -1722,15 +1781,15 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
   float* ws = static_cast<float*>(workspace);
   p.part = split ? ws : nullptr;
   for (int i = 0; i < nseg; ++i) p.seg[i].tile_partials = split ? nullptr : ws + ws_off[i];
+  int32_t most = 0;  // chunks of the widest segment: one wavefront each, up to kReduceWaves
+  for (int i = 0; i < nseg; ++i) most = p.seg[i].nchunks > most ? p.seg[i].nchunks : most;
+  p.reduce_waves = most < kReduceWaves ? most : kReduceWaves;
   hipStream_t st = static_cast<hipStream_t>(stream);
   void* args[] = {&p};
   if (hipLaunchKernel(gemm, dim3(static_cast<unsigned>(grid)), dim3(block), args, 0, st) !=
       hipSuccess)
     return QKN_EHIP;
   if (split) {
-    int64_t most = 0;  // chunks of the widest segment: one wavefront each, up to kReduceWaves
-    for (int i = 0; i < nseg; ++i) most = p.seg[i].nchunks > most ? p.seg[i].nchunks : most;
-    const int waves = most < kReduceWaves ? static_cast<int>(most) : kReduceWaves;
 #define QKN_REDUCE(n)                                           \
   (many ? reinterpret_cast<const void*>(qkn_proj_reduce_many<n>) \
         : reinterpret_cast<const void*>(qkn_proj_reduce<n>))
@@ -1741,7 +1800,7 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
                                           : QKN_REDUCE(16);
 #undef QKN_REDUCE
     if (hipLaunchKernel(reduce, dim3(static_cast<unsigned>(T), static_cast<unsigned>(nseg)),
-                        dim3(64 * waves), args, 0, st) != hipSuccess)
+                        dim3(64 * p.reduce_waves), args, 0, st) != hipSuccess)
       return QKN_EHIP;
   } else {
     const dim3 fgrid(static_cast<unsigned>((T + 255) / 256), static_cast<unsigned>(nseg));
