@@ -49,7 +49,7 @@ struct FormatInfo {
 constexpr FormatInfo kFormat[2] = {{2, 8, 8, {16, 32}, "", 24 * 1024, 1},
                                    {1, 16, 4, {8, 16}, "_fp8", 28 * 1024, 4}};
 
-constexpr int kAnyWavesPerBlock = 4;  // rows of any alignment: workgroup size in wavefronts
+constexpr int kAnyWavesPerBlock = 4;  // rows of any alignment, long launches of one phase: workgroup size in wavefronts
 
 constexpr int kMaxWideLdsBytes = 64 * 1024;  // gamma of both tensors staged by the wide path
 
@@ -415,7 +415,14 @@ int launch(const HSeg* segs, int nseg, int tp, int rank, int64_t T, float eps, i
     // over; short launches (decode) spread one-wave workgroups over more CUs.
     // Rows of any alignment: four-wave ones in bf16 too (1100 + 100 columns,
     // 7999 tokens 10.3 against 11.0 us; 2200 + 1001, 8192 tokens 19.4 against 21.0)
-    const int many = any ? kAnyWavesPerBlock : fi.waves_per_block;
+    // bf16 apply and Phase A alone: four-wave ones too (12001 tokens of 1280 + 256
+    // columns, both phases 28.9 -> 27.8 us), from 32 tokens per CU (6200 of 128
+    // Phase A 3.3 against 3.5 us in one-wave groups) and up to 3072 columns, where
+    // whole groups of four leave the wavefronts per CU about what is wanted (8192
+    // of 2048 apply 13.2 -> 13.0 us, 12001 of 3000 the same, 20000 of 4096 54.0
+    // against 55.9).
+    const bool groups = mode != kFused && kp.seg[0].d <= 3072 && T >= static_cast<int64_t>(cus) * 32;
+    const int many = any || groups ? kAnyWavesPerBlock : fi.waves_per_block;
     if (g_opt_waves_per_block > 0) wpb = static_cast<int>(g_opt_waves_per_block);
     else if (T >= static_cast<int64_t>(cus) * many * kMinWavesPerCu)
       wpb = many;

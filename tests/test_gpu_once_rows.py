@@ -91,3 +91,26 @@ def test_a_wavefront_per_token(case):
         else:
             compare.check_close(Q.decode_bf16(y), ref["y"][:keep], compare.OUTPUT_RTOL, "y")
         compare.check_close(s.partials.cpu().numpy()[rank], ref["partials"][rank], compare.PARTIAL_RTOL, "own partial")
+
+
+@pytest.mark.parametrize("T,d", [(8191, 1280), (8192, 8), (8193, 1032), (8197, 3072), (8197, 3080)])
+def test_four_wave_groups_of_one_phase(T, d):
+    print(f"[groups] {T} {d}", flush=True)
+    x = torch.randn(T, d, device=DEV).bfloat16()
+    w = torch.randn(d, device=DEV)
+    out = []
+    for wpb in (0, 1):
+        L.qkn_set_option("waves_per_block", wpb)
+        try:
+            P = torch.zeros(2, T, device=DEV)
+            L.qkn_partial_sumsq(x, out=P[0])
+            y = L.qkn_apply(x, w, P, 2 * d, 1e-6)
+            info = L.qkn_last_launch()
+        finally:
+            L.qkn_set_option("waves_per_block", 0)
+        out.append((bits_of(y), _bits(P)))
+        # the rule holds on the 256 CUs of the card
+        assert info["block"] == (256 if wpb == 0 and T >= 8192 and d <= 3072 else 64), info
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    pos = x.double().square().sum(1).float()
+    assert torch.allclose(torch.from_numpy(out[0][1].view(np.float32))[0], pos.cpu(), rtol=compare.PARTIAL_RTOL, atol=0)
