@@ -275,6 +275,28 @@ __device__ __forceinline__ void epilogue16(const ProjParams& p, const ProjSegDev
   epilogue_staged<64 * WMB, 128, OUT_ROW>(p, s, out, m0, n0, rows_a, rows_b);
 }
 
+// Sum of squares of 64 staged columns in ascending order. EDGE: those from
+// `valid` on (a multiple of 8) count as zero. They would hold zeros anyway as
+// long as the offset of a row of W past the segment is behind the descriptor;
+// with rows of 2^25 elements or more that 32-bit offset wraps, and they hold
+// products with other rows of W.
+template <bool EDGE>
+__device__ __forceinline__ float half_chunk_sumsq(const uint16_t* src, int valid) {
+  float acc = 0.0f;
+#pragma unroll
+  for (int c = 0; c < 64; c += 8) {
+    u32x4 v = *reinterpret_cast<const u32x4*>(src + c);
+    if (EDGE && c >= valid) v = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float lo = bf16_lo(v[e]), hi = bf16_hi(v[e]);
+      acc = __builtin_fmaf(lo, lo, acc);
+      acc = __builtin_fmaf(hi, hi, acc);
+    }
+  }
+  return acc;
+}
+
 // Stores and statistic of a tile staged in LDS as bf16 ([BM][OUT_ROW]).
 template <int BM, int BN, int OUT_ROW, int THREADS>
 __device__ __forceinline__ void epilogue_staged(const ProjParams& p, const ProjSegDev& s,
@@ -306,18 +328,9 @@ __device__ __forceinline__ void epilogue_staged(const ProjParams& p, const ProjS
     const int row = rc % BM, chunk = rc / BM;
     const uint16_t* src = out + row * OUT_ROW + chunk * kChunkN + half * 64;
     float acc_s = 0.0f;
-    if (live) {
-#pragma unroll
-      for (int c = 0; c < 64; c += 8) {
-        const u32x4 v = *reinterpret_cast<const u32x4*>(src + c);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float lo = bf16_lo(v[e]), hi = bf16_hi(v[e]);
-          acc_s = __builtin_fmaf(lo, lo, acc_s);
-          acc_s = __builtin_fmaf(hi, hi, acc_s);
-        }
-      }
-    }
+    if (live)
+      acc_s = rows_b == BN ? half_chunk_sumsq<false>(src, 64)
+                           : half_chunk_sumsq<true>(src, rows_b - chunk * kChunkN - half * 64);
     // the partner lane's sum (quad_perm [1,0,3,2]: lanes 2u and 2u+1 swap)
     const float other = __builtin_bit_cast(
         float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, acc_s), 0xB1, 0xF, 0xF, false));

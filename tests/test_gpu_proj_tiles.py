@@ -112,3 +112,22 @@ def test_a_nan_stays_in_its_row_and_column():
     want[700, :] = True
     want[:, 131] = True
     assert np.array_equal(bad, want)
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2, 3])
+@pytest.mark.parametrize("T,h", [(130, 128), (1100, 72)])
+def test_weight_rows_far_apart(T, h, tile):
+    """Rows of W 2^26 bytes apart: 64 of them span 2^32 bytes, so the 32-bit offset of a row past the
+    segment comes back to a valid one. The columns it makes must not reach the statistic."""
+    g = torch.Generator(device=DEV).manual_seed(T)
+    x = torch.randn(T, h, device=DEV, generator=g).bfloat16()
+    near = (torch.randn(8, h, device=DEV, generator=g) * h ** -0.5).bfloat16()
+    far = torch.as_strided(torch.zeros(7 * (1 << 25) + h, dtype=torch.bfloat16, device=DEV), (8, h), (1 << 25, 1))
+    far.copy_(near)
+    print(f"[far] {T} {h} {tile}", flush=True)
+    (want,), _ = _run(x, [near], 0, tile)
+    (got,), _ = _run(x, [far], 0, tile)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    xr, wb = bits_of(x), bits_of(near)
+    err = np.abs(got[1].astype(np.float64) - P.stored_partials(xr, wb))
+    assert np.all(err <= compare.projection_partial_bound(P.project(xr, wb), P.dot_abs(xr, wb), h))
