@@ -289,8 +289,18 @@ const char* qkn_strerror(int status);
  * for tests and benchmarks. kernel is a static string naming the variant
  * ("rows<4,1>/fused", "wide<16,2>/fused", "generic/apply", "rows_fp8<2,1>/fused",
  * ...; the numbers are 16-byte chunks per lane); grid is in workgroups, block in
- * threads, waves = grid * block / 64, lds_bytes is the dynamic LDS per
- * workgroup.
+ * threads, waves = grid * block / 64, lds_bytes is the LDS per workgroup (of
+ * the norm kernels, which have no other, the dynamic one).
+ *   "rows"     both register-path kernels: with a loop over tokens, and without
+ *              one (only where waves equals the number of tokens);
+ *   "generic"  any width and alignment: rows staged in LDS, or held in
+ *              registers (a fused launch then has lds_bytes 0);
+ *   "proj"     <tile, k per LDS stage, LDS stages filled directly ("dl2",
+ *              "dl4") or from registers ("reg"), "mi16" for 16 x 16 x 32 MFMAs
+ *              in an unsplit launch, "splitk">. A 256 x 256 launch has
+ *              128 x 128 tiles too where large ones do not fit. A
+ *              validate_only call names kernel 1 of "proj_tile" for every
+ *              unsplit launch, whose results all of them have.
  */
 typedef struct qkn_launch_info {
   const char* kernel;
@@ -332,9 +342,9 @@ int qkn_last_launch(qkn_launch_info* info);
  *   "force_generic"  1 = always take the general path's staged kernel (same
  *                    results);
  *   "proj_tile"      qkn_proj_partial's kernel: 0 = automatic (split k for
- *                    decode-sized launches; else kernel 1, or 256 x 256 tiles
- *                    of 512 threads with the same results where those are
- *                    faster, reported under kernel 1's name), 1 = direct-to-
+ *                    decode-sized launches; else kernel 1, or the large-tile
+ *                    kernel of 512 threads with the same results where that
+ *                    is faster), 1 = direct-to-
  *                    LDS two-stage kernel on 16 x 16 x 32 MFMAs, never split,
  *                    2 = register-staged kernel, never split, 3 = direct-to-
  *                    LDS kernel on 32 x 32 x 16 MFMAs, never split (2 and 3

@@ -1158,6 +1158,13 @@ __device__ __forceinline__ void acc_to_lds(const f32x4 (&acc)[C::kMi][C::kNi], f
           acc[i][j];
 }
 
+template <int TM, int S>
+struct SplitCfg {
+  static constexpr int kRow = 128 + 4;  // fp32 per row of the tile staged for the stores
+  static constexpr int kStages = S == 4 ? DuoCfg<TM, S>::kLds : BigCfg<TM, 128>::kLds;
+  static constexpr int kLds = kStages > TM * kRow * 4 ? kStages : TM * kRow * 4;
+};
+
 // Split k: a workgroup takes one k-slice of one TM x 128 tile with the
 // role-split loop on four stages, or the eight-wavefront one on two (two or
 // three workgroups per CU), and stores its fp32 sums into the slice array
@@ -1169,10 +1176,8 @@ __device__ __forceinline__ void acc_to_lds(const f32x4 (&acc)[C::kMi][C::kNi], f
 template <int TM, int S>
 __global__ __launch_bounds__(kBigThreads, S == 2 ? 4 : 2) void qkn_proj_gemm_split(const ProjParams p) {
   constexpr bool kDuo = S == 4;
-  constexpr int kStages = kDuo ? DuoCfg<TM, S>::kLds : BigCfg<TM, 128>::kLds;
-  constexpr int kRow = 128 + 4;  // fp32 per row of the tile staged for the stores
-  constexpr int kLds = kStages > TM * kRow * 4 ? kStages : TM * kRow * 4;
-  __shared__ __align__(1024) unsigned char lds[kLds];
+  constexpr int kRow = SplitCfg<TM, S>::kRow;
+  __shared__ __align__(1024) unsigned char lds[SplitCfg<TM, S>::kLds];
   const int b = xcd_run(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
   // slice-major runs: an XCD's workgroups share the slice's columns of x and W
   const int tiles = p.m_tiles * p.n_tiles;
@@ -1737,11 +1742,13 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
       if (grid > kCus) {
         gemm = reinterpret_cast<const void*>(qkn_proj_gemm_split<64, 2>);
         block = kBigThreads;
+        name = "proj<64x128,64,dl2,splitk>";
+        lds = SplitCfg<64, 2>::kLds;
       } else {
         gemm = reinterpret_cast<const void*>(qkn_proj_gemm_decode);
+        name = "proj<64x128,64,dl4,splitk>";
+        lds = DlCfg<1, kSplitBk, kSplitStages>::kLdsBytes;
       }
-      name = "proj<64x128,64,dl4,splitk>";
-      lds = DlCfg<1, kSplitBk, kSplitStages>::kLdsBytes;
     } else {
       // Two workgroups per CU of eight multiplying wavefronts on two-stage
       // rings, or one on a four-stage ring with the roles split. Measured at
@@ -1759,8 +1766,8 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
                                           : nk <= 4 || (nk <= 8 && p.m_tiles > 1);
       gemm = two ? reinterpret_cast<const void*>(qkn_proj_gemm_split<128, 2>)
                  : reinterpret_cast<const void*>(qkn_proj_gemm_split<128, 4>);
-      name = "proj<128x128,64,dl4,splitk>";
-      lds = DuoCfg<128, 4>::kLds;
+      name = two ? "proj<128x128,64,dl2,splitk>" : "proj<128x128,64,dl4,splitk>";
+      lds = two ? SplitCfg<128, 2>::kLds : SplitCfg<128, 4>::kLds;
       block = kBigThreads;
     }
   } else {
@@ -1768,9 +1775,11 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
     if (tiles > max_wgs) return QKN_ENOTSUP;
     grid = round8(tiles);
   }
+  // a validate-only call names kernel 1 for every unsplit launch, whose results
+  // all of them have bit for bit; a launch names the kernel that ran
+  const qkn_launch_info planned{name, 0, 0, 0, lds};
   if (!split && g_tile_choice == 0) {
-    // the large-tile kernel where it is faster; it reports kernel 1's name,
-    // whose results it gives bit for bit (512 threads tell it apart)
+    // the large-tile kernel where it is faster
     const int64_t nk = (hidden + 63) / 64;
     int64_t time = 0;
     p.big = big_grid(T, nk, segs, nseg, &time);
@@ -1779,12 +1788,13 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
       gemm = reinterpret_cast<const void*>(qkn_proj_gemm_big);
       grid = static_cast<int64_t>(p.big.whole) + p.big.smalls;
       block = kBigThreads;
+      name = p.big.whole ? "proj<256x256,64,dl2,mi16>" : "proj<128x128,64,dl4,mi16>";
       lds = kBigLds;
     }
   }
   const qkn_launch_info info{name, grid, block, grid * (block / 64), lds};
   if (qkn_host::validate_only()) {
-    qkn_host::record_launch(qkn_launch_info{info.kernel, 0, 0, 0, info.lds_bytes});
+    qkn_host::record_launch(planned);
     return QKN_EDRYRUN;
   }
   if (use_scratch) {

@@ -49,18 +49,31 @@ def _tree(y):
     return S
 
 
-@pytest.mark.parametrize("T,hidden,dq,dk", [
-    (1, 256, 128, 8), (64, 4096, 1032, 248), (64, 2048, 2560, 0), (63, 1096, 4096, 1024), (17, 8192, 2048, 640),
-    (65, 264, 136, 0), (128, 1024, 2056, 520), (129, 4096, 264, 128), (300, 1096, 2048, 512), (512, 520, 4096, 1024),
-    (777, 2048, 1280, 256), (777, 1344, 2048, 512), (1024, 640, 4104, 1000), (200, 4096, 4096, 1024),
+# what a launch reports of each kernel: name, threads, LDS bytes
+FORMS = {
+    "decode": ("proj<64x128,64,dl4,splitk>", 256, 4 * (64 + 128) * 128),
+    "two64": ("proj<64x128,64,dl2,splitk>", 512, 2 * (64 + 128) * 128),
+    "two128": ("proj<128x128,64,dl2,splitk>", 512, 128 * 132 * 4),  # the fp32 tile is larger than the stages
+    "roles": ("proj<128x128,64,dl4,splitk>", 512, 4 * (128 + 128) * 128),
+}
+
+
+@pytest.mark.parametrize("T,hidden,dq,dk,form", [
+    (1, 256, 128, 8, "decode"), (64, 4096, 1032, 248, "decode"), (64, 2048, 2560, 0, "two64"),
+    (63, 1096, 4096, 1024, "two64"), (17, 8192, 2048, 640, "two64"), (65, 264, 136, 0, "roles"),
+    (128, 1024, 2056, 520, "two128"), (129, 4096, 264, 128, "roles"), (300, 1096, 2048, 512, "roles"),
+    (512, 520, 4096, 1024, "two128"), (777, 2048, 1280, 256, "roles"), (777, 1344, 2048, 512, "two128"),
+    (1024, 640, 4104, 1000, "two128"), (200, 4096, 4096, 1024, "two128"),
+    (777, 8192, 2048, 512, "roles"), (384, 8192, 4096, 1024, "two128"), (500, 4096, 4096, 1024, "roles"),
 ])
-def test_split_k(T, hidden, dq, dk):
+def test_split_k(T, hidden, dq, dk, form):
     g = torch.Generator(device=DEV).manual_seed(T + hidden)
     x = torch.randn(T, hidden, device=DEV, generator=g).bfloat16()
     ws = [(torch.randn(d, hidden, device=DEV, generator=g) * hidden ** -0.5).bfloat16() for d in (dq, dk) if d]
     print(f"[split] {T} {hidden} {dq} {dk}", flush=True)
     outs, info = _run(x, ws)
     assert info["kernel"].endswith("splitk>"), info
+    assert (info["kernel"], info["block"], info["lds_bytes"]) == FORMS[form], info
     again, _ = _run(x, ws)
     rows = np.unique(np.clip(np.r_[0:3, 62:66, 126:130, T // 2, T - 3:T], 0, T - 1))
     xr = bits_of(x)[rows]

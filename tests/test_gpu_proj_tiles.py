@@ -65,9 +65,11 @@ def test_large_tiles_match_128(case):
     ws = [(torch.randn(d, h + 8, device=DEV, generator=g) * h ** -0.5).bfloat16()[:, 8:] for d in (dq, dk) if d]
     print(f"[tiles] {case}", flush=True)
     got, info = _run(x, ws, gap, 0)
-    assert info["block"] == 512, info
+    assert info["block"] == 512 and info["lds_bytes"] == 256 * 264 * 2, info
+    # the smaller cases have no large tile
+    assert info["kernel"] == ("proj<256x256,64,dl2,mi16>" if T >= 2560 else "proj<128x128,64,dl4,mi16>"), info
     ref, info1 = _run(x, ws, gap, 1)
-    assert info1["block"] == 256, info1
+    assert info1["block"] == 256 and info1["kernel"] == "proj<128x128,64,dl2,mi16>", info1
     for (y, part), (ry, rp) in zip(got, ref):
         assert np.array_equal(y, ry)
         assert np.array_equal(part, rp)
