@@ -64,6 +64,9 @@ FORMS = {
     (128, 1024, 2056, 520, "two128"), (129, 4096, 264, 128, "roles"), (300, 1096, 2048, 512, "roles"),
     (512, 520, 4096, 1024, "two128"), (777, 2048, 1280, 256, "roles"), (777, 1344, 2048, 512, "two128"),
     (1024, 640, 4104, 1000, "two128"), (200, 4096, 4096, 1024, "two128"),
+    # slices of 3, 5, 6, 7 and 9 stages: the role-split ring ends at each of its slots
+    (130, 1480, 256, 128, "roles"), (100, 5120, 1024, 256, "roles"), (257, 1496, 384, 0, "roles"),
+    (200, 3344, 256, 8, "roles"), (640, 1112, 512, 0, "roles"),
     (777, 8192, 2048, 512, "roles"), (384, 8192, 4096, 1024, "two128"), (500, 4096, 4096, 1024, "roles"),
 ])
 def test_split_k(T, hidden, dq, dk, form):
