@@ -1755,19 +1755,21 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
       }
     } else {
       // Two workgroups per CU of eight multiplying wavefronts on two-stage
-      // rings, or one on a four-stage ring with the roles split. Measured at
-      // hidden 4096 unless said, role-split time first: up to one workgroup per
-      // CU the latter (512 tokens, 1536 columns 17.5 against 21.4 us) unless a
-      // slice has two stages or fewer (hidden 1024, 100 tokens, 768 columns 9.5
-      // against 8.6); up to two per CU the former (384 tokens, 5120 columns 38.8
-      // against 35.9) unless the second round is small and the slices long (777
-      // tokens, hidden 8192, 2560 columns 59.5 against 70.9); beyond, the former
-      // for short slices (128 tokens, 5120 columns 34.6 against 32.9; 512 tokens
-      // 54.2 against 56.0).
+      // rings, or one on a four-stage ring with the roles split. Measured with
+      // weights from HBM, role-split time first. Up to one workgroup per CU the
+      // latter (384 tokens, hidden 4096, 1792 columns 22.1 against 27.8 us)
+      // unless a slice has two stages or fewer (hidden 1024, 100 tokens, 1792
+      // columns 11.4 against 11.2). Up to two per CU the former (384 tokens,
+      // hidden 8192, 3584 columns 52.9 against 46.4; 1024 tokens, hidden 4096,
+      // 2560 columns 54.3 against 50.8), unless the second round is nearly
+      // empty and the slices long (777 tokens, hidden 3072, 2560 columns 34.8
+      // against 36.5). Beyond, the former for slices of up to 12 stages (128
+      // tokens, hidden 7168, 5120 columns 42.5 against 40.1; 512 tokens, hidden
+      // 3072 48.9 against 47.6).
       const int nk = (pl.kslice + 63) / 64;
       const bool two = grid <= kCus       ? nk <= 2
-                       : grid <= 2 * kCus ? nk < 32 || 2 * grid >= 3 * kCus
-                                          : nk <= 4 || (nk <= 8 && p.m_tiles > 1);
+                       : grid <= 2 * kCus ? nk < 12 || 4 * grid >= 5 * kCus
+                                          : nk <= 12;
       gemm = two ? reinterpret_cast<const void*>(qkn_proj_gemm_split<128, 2>)
                  : reinterpret_cast<const void*>(qkn_proj_gemm_split<128, 4>);
       name = two ? "proj<128x128,64,dl2,splitk>" : "proj<128x128,64,dl4,splitk>";

@@ -68,6 +68,7 @@ FORMS = {
     (130, 1480, 256, 128, "roles"), (100, 5120, 1024, 256, "roles"), (257, 1496, 384, 0, "roles"),
     (200, 3344, 256, 8, "roles"), (640, 1112, 512, 0, "roles"),
     (777, 8192, 2048, 512, "roles"), (384, 8192, 4096, 1024, "two128"), (500, 4096, 4096, 1024, "roles"),
+    (100, 5120, 4096, 1024, "two128"), (1024, 4096, 2048, 512, "two128"), (777, 2048, 2048, 512, "roles"),
 ])
 def test_split_k(T, hidden, dq, dk, form):
     g = torch.Generator(device=DEV).manual_seed(T + hidden)
