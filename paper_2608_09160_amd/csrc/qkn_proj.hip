@@ -1302,11 +1302,15 @@ __global__ __launch_bounds__(kThreads) void qkn_proj_gemm_decode(const ProjParam
 // tokens, hidden 4096, 1024 + 256 columns (projection and norm): arguments
 // asked for at once here and in the slices' kernel, a chunk's LDS reads ahead of
 // its chain, and statistics a lane each, 253.5 -> 247.9 us.
+// Eight LDS reads ahead of the chain and not all sixteen: with the 66 registers
+// of those, two workgroups of sixteen wavefronts did not fit a CU, and 257 to
+// 512 of them ran in two rounds (384 tokens, hidden 2048, one segment of 2560
+// columns, the whole call 21.2 -> 20.5 us).
 constexpr int kMaxSplitChunks = 2048;  // 128-column chunks of both segments
 constexpr int kMaxSplits = 16;         // slices: (row tiles) x (slices) <= 16
 constexpr int kReduceWaves = 16;
 template <int SPLITS>
-__global__ __launch_bounds__(64 * kReduceWaves) void qkn_proj_reduce(const ProjParams p) {
+__global__ __launch_bounds__(64 * kReduceWaves, 8) void qkn_proj_reduce(const ProjParams p) {
   __shared__ __align__(16) float vals[kReduceWaves][kChunkN];
   __shared__ float chunk_sum[kMaxSplitChunks];
   want_reduce_params(p);
@@ -1344,14 +1348,16 @@ __global__ __launch_bounds__(64 * kReduceWaves) void qkn_proj_reduce(const ProjP
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const f32x4* h = reinterpret_cast<const f32x4*>(v + (lane & 1) * 64);
-    f32x4 x[16];
+    f32x4 x[8];  // read eight vectors ahead of the chain
 #pragma unroll
-    for (int i = 0; i < 16; ++i) x[i] = h[i];
+    for (int i = 0; i < 8; ++i) x[i] = h[i];
     float acc_s = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
+    for (int i = 0; i < 16; ++i) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc_s = __builtin_fmaf(x[i][e], x[i][e], acc_s);
+      for (int e = 0; e < 4; ++e) acc_s = __builtin_fmaf(x[i % 8][e], x[i % 8][e], acc_s);
+      if (i < 8) x[i] = h[i + 8];
+    }
     const float other = __builtin_bit_cast(
         float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, acc_s), 0xB1, 0xF, 0xF, false));
     if (lane == 0) chunk_sum[q] = acc_s + other;

@@ -1,4 +1,6 @@
 """The build's guard against kernels that use scratch memory (host logic only)."""
+import os
+
 import pytest
 
 from paper_2608_09160_amd import build as B
@@ -34,3 +36,15 @@ def test_scratch_or_vector_spills_fail_the_build():
         B.check_resources(res)
     # scalar spills go to vector-register lanes, not memory: allowed
     B.check_resources({"k_clean": res["k_clean"]})
+
+
+def test_two_workgroups_of_the_reduction_fit_a_cu():
+    """The split-k reductions run in workgroups of up to 16 wavefronts. Two of them on a CU are 8 wavefronts
+    on each of its 4 SIMDs: at most 512 / 8 = 64 registers."""
+    path = os.path.join(B.PKG_DIR, "_build", "kernel_resources.txt")
+    if not os.path.exists(path):
+        pytest.skip("the library was not built here")
+    lines = [line for line in open(path) if "qkn_proj_reduce" in line]
+    assert len(lines) == 8  # two kernels, four slice counts each
+    for line in lines:
+        assert "Occupancy [waves/SIMD]=8" in line, line
