@@ -1583,6 +1583,7 @@ int64_t time_small(int64_t rounds, int64_t nk, bool strips) {
   return rounds * ((rounds > 1 ? 1050 : 750) + (strips ? 45 : 33) * nk);
 }
 constexpr int64_t kShallow = 16;  // stages below which only single rounds take the large-tile kernel
+constexpr int32_t kWideTiles = 40;  // 128-column tiles from which one two-stage round is left as it is
 int64_t time_two_stage(int64_t rounds, int64_t nk) { return 800 + 105 * nk * rounds; }
 int64_t rounds_of(int64_t tiles, int64_t per_round) { return (tiles + per_round - 1) / per_round; }
 
@@ -1804,7 +1805,13 @@ int proj_impl(const uint16_t* x, int64_t ldx, int64_t T, int64_t hidden,
     int64_t time = 0;
     p.big = big_grid(T, nk, segs, nseg, &time);
     const int64_t tiles = static_cast<int64_t>(p.m_tiles) * p.n_tiles;
-    if (time < time_two_stage(rounds_of(tiles, 2 * kCus), nk) && (nk >= kShallow || tiles <= kCus)) {
+    // one round of the two-stage kernel over many columns of few rows: weights
+    // that come from HBM, as in a model of many layers, bound it less (1280
+    // tokens x 5120 columns, hidden 4096: 70.6 against 79.2 us, hidden 5120 87.8
+    // against 105.5; weights left in the last-level cache by the call before:
+    // 67.8 against 62.0). 1025 to 1152 tokens show no difference.
+    const bool wide = tiles > kCus && tiles <= 2 * kCus && p.n_tiles >= kWideTiles;
+    if (!wide && time < time_two_stage(rounds_of(tiles, 2 * kCus), nk) && (nk >= kShallow || tiles <= kCus)) {
       gemm = reinterpret_cast<const void*>(qkn_proj_gemm_big);
       grid = static_cast<int64_t>(p.big.whole) + p.big.smalls;
       block = kBigThreads;

@@ -133,3 +133,17 @@ def test_weight_rows_far_apart(T, h, tile):
     xr, wb = bits_of(x), bits_of(near)
     err = np.abs(got[1].astype(np.float64) - P.stored_partials(xr, wb))
     assert np.all(err <= compare.projection_partial_bound(P.project(xr, wb), P.dot_abs(xr, wb), h))
+
+
+@pytest.mark.parametrize("T,dq,dk,name", [(1280, 4096, 1024, "proj<128x128,64,dl2,mi16>"),
+                                          (1280, 4096, 768, "proj<128x128,64,dl4,mi16>"),
+                                          (1700, 4096, 1024, "proj<256x256,64,dl2,mi16>")])
+def test_many_columns_of_few_rows(T, dq, dk, name):
+    """One round of 128 x 128 tiles from 40 column tiles on stays in the two-stage kernel."""
+    g = torch.Generator(device=DEV).manual_seed(T + dk)
+    x = torch.randn(T, 4096, device=DEV, generator=g).bfloat16()
+    ws = [(torch.randn(d, 4096, device=DEV, generator=g) / 64).bfloat16() for d in (dq, dk)]
+    got, info = _run(x, ws, 0, 0)
+    assert info["kernel"] == name, info
+    for (y, part), (ry, rp) in zip(got, _run(x, ws, 0, 1)[0]):
+        assert np.array_equal(y, ry) and np.array_equal(part, rp)
