@@ -273,6 +273,27 @@ DevSeg to_dev(const HSeg& s, int mode, const FormatInfo& fi) {
   return d;
 }
 
+// Launches of a wavefront per token that the kernels with a loop run faster.
+// Those ask for gamma first, the ones without a loop for the rows, which pays
+// while a CU has few wavefronts; with more of them gamma, behind the rows in
+// every wavefront's queue, is what they wait for. It shows with four chunks per
+// lane and a short sum over the ranks (loop's time last):
+//   bf16, two tensors, the second of one chunk, tp = 1, above 4.75 tokens per CU
+//     (1536 tokens of 2048 + 512 columns 5.06 against 4.86 us, of 2048 + 256
+//     4.80 against 4.48; 1216 tokens the same in both; tp 2 and more 2 to 12 %
+//     for the kernel without a loop);
+//   fp8, whose gamma is four times the row, at 2.25 to 4.25 tokens per CU
+//     (apply, 896 tokens of 4096 columns, tp 1 to 4, by 4 to 6 %; fused, 896
+//     tokens of 4096 + 1024, tp 1, by 1 to 4 %, of 4096 + 2048, tp 2, by 3 %; on
+//     either side of the range and at higher tp the other way).
+bool loop_anyway(int fmt, int mode, int idx0, int i1, int tp, int64_t T, int cus) {
+  if (kNVal[idx0] != 4) return false;
+  const int64_t quarters = 4 * T;  // tokens in quarters, against the CUs
+  if (fmt == kBf16) return mode == kFused && i1 == 1 && tp == 1 && quarters > int64_t{19} * cus;
+  if (quarters <= int64_t{9} * cus || quarters > int64_t{17} * cus) return false;
+  return mode == kApply ? tp <= 4 : mode == kFused && tp <= (i1 >= 2 ? 2 : i1);
+}
+
 // Arguments of the waiting and publishing modes.
 struct WaitArgs {
   uint64_t* slots[2];
@@ -478,10 +499,11 @@ int launch(const HSeg* segs, int nseg, int tp, int rank, int64_t T, float eps, i
   // A wavefront for every token: the kernels without a loop (per graph node, 256
   // tokens of 640 + 128 columns 2.9 against 3.2 us, 3000 of 256 + 128 3.9
   // against 4.5; the most one round takes, 1536 tokens, of 4096 + 1024 columns
-  // 6.9 against 7.8, of 2048 + 512 5.2 against 5.1). Longer launches keep the
-  // loop: with the same argument loads ahead of it, 8192 tokens of 2048 + 512
-  // columns took 15.9 against 15.8 us in bf16 and 10.4 against 10.0 in fp8.
-  if (fast && !waits && block == kWave && grid == T && !g_opt_prefetch && !g_opt_token_blocks) {
+  // 6.7 against 7.5). Longer launches keep the loop: with the same argument
+  // loads ahead of it, 8192 tokens of 2048 + 512 columns took 15.9 against 15.8
+  // us in bf16 and 10.4 against 10.0 in fp8.
+  if (fast && !waits && block == kWave && grid == T && !g_opt_prefetch && !g_opt_token_blocks &&
+      !loop_anyway(fmt, mode, idx[0], i1, tp, T, cus)) {
     if (mode == kFused) fn = reinterpret_cast<const void*>(kOnceFusedTable[fmt][idx[0]][i1]);
     else if (mode == kApply) fn = reinterpret_cast<const void*>(kOnceApplyTable[fmt][idx[0]]);
     else fn = reinterpret_cast<const void*>(kOncePartialTable[fmt][idx[0]]);

@@ -25,6 +25,9 @@ CASES = [  # (dtype, tokens, ranks, rank, Q width, K width; 0: one tensor)
     ("bf16", 1, 1, 0, 8, 0), ("bf16", 3, 2, 1, 512, 128), ("bf16", 64, 3, 0, 520, 1032), ("bf16", 65, 4, 3, 1024, 256),
     ("bf16", 257, 5, 4, 640, 2048), ("bf16", 300, 8, 5, 2056, 512), ("bf16", 5, 9, 8, 4096, 4096),
     ("bf16", 7, 64, 63, 128, 4088), ("bf16", 1536, 2, 0, 4096, 1024), ("bf16", 1537, 2, 0, 4096, 1024),
+    # either side of the launches that keep the loop all the same
+    ("bf16", 1216, 1, 0, 2048, 512), ("bf16", 1217, 1, 0, 2048, 512), ("fp8", 576, 2, 1, 4096, 2048),
+    ("fp8", 577, 2, 1, 4096, 2048), ("fp8", 1088, 4, 0, 4096, 0), ("fp8", 1089, 4, 0, 4096, 0),
     ("fp8", 1, 1, 0, 16, 0), ("fp8", 9, 4, 2, 1024, 1040), ("fp8", 256, 8, 7, 2064, 128), ("fp8", 33, 6, 0, 4096, 4096),
 ]
 
