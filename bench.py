@@ -388,9 +388,11 @@ def traffic_bytes(kernel: str, workload: str):
         return None
 
 
-def trace_name(launch_name: str) -> str:
+def trace_name(launch_name: str, loop: bool = True) -> str:
     """Profiler (demangled) name of the kernel a launch name denotes, e.g.
-    "rows<4,1>/fused" -> "void qkn_rows<FmtBf16, 4, 1, 0, 0>"."""
+    "rows<4,1>/fused" -> "void qkn_rows<FmtBf16, 4, 1, 0, 0>". loop=False: the
+    register path's kernel without a loop over tokens, which launches of a
+    wavefront per token run under the same launch name."""
     import re
     m = re.fullmatch(r"(rows|wide)(_pf|_pa|_pa2|_pa3)?(_fp8)?<(\d+),(\d+)>/"
                      r"(fused|apply|partial|fused_wait|publish)", launch_name)
@@ -399,18 +401,23 @@ def trace_name(launch_name: str) -> str:
     fam, sched_tag, fp8, n0, n1, mode = m.groups()
     fmt = "FmtFp8" if fp8 else "FmtBf16"
     mode_id = ["fused", "apply", "partial", "fused_wait", "publish"].index(mode)
+    if not loop and (fam == "wide" or sched_tag or mode_id > 2):
+        raise ValueError(f"{launch_name!r} always has a loop over tokens")
     if fam == "wide":
         return f"void qkn_wide<{fmt}, {n0}, {n1}, {mode_id}>"
+    if not loop:
+        return f"void qkn_rows_once<{fmt}, {n0}, {n1}, {mode_id}>"
     sched = {None: 0, "_pf": 1, "_pa": 2, "_pa2": 3, "_pa3": 4}[sched_tag]
     return f"void qkn_rows<{fmt}, {n0}, {n1}, {mode_id}, {sched}>"
 
 
 def kernel_base_name(profiler_name: str) -> str:
-    """Profiler name without namespaces and parameter list, e.g.
-    "void qkn_dev::qkn_rows<qkn_dev::FmtBf16, 4, 1, 0, 0>(qkn_dev::KParams)"
+    """Profiler name without namespaces, parameter list and qkn_rows' default
+    last argument (aligned rows; `true` is kept), e.g.
+    "void qkn_dev::qkn_rows<qkn_dev::FmtBf16, 4, 1, 0, 0, false>(qkn_dev::KParams)"
     -> "void qkn_rows<FmtBf16, 4, 1, 0, 0>"."""
     return (profiler_name.replace("(anonymous namespace)::", "").replace("qkn_dev::", "")
-            .split("(")[0])
+            .split("(")[0].replace(", false>", ">"))
 
 
 def summarize(outdir: str) -> None:
@@ -472,7 +479,8 @@ def summarize(outdir: str) -> None:
              f"{algo / (mean_us * 1e-6) / 1e9:.0f} GB/s = {algo / (mean_us * 1e-6) / 1e9 / HBM_PEAK_GBS:.1%} "
              f"of 8 TB/s. The traced bench.py line (tracing adds gaps between launches): kernel_us "
              f"{bench['roofline']['kernel_us']} (timed region / launches)."] + plain + [
-             "", "Kernel names: `qkn_rows<Fmt, N0, N1, MODE, SCHED>` / `qkn_wide<Fmt, N0, N1, MODE>`, "
+             "", "Kernel names: `qkn_rows<Fmt, N0, N1, MODE, SCHED>` (a last `true`: rows of any alignment) / "
+             "`qkn_rows_once<Fmt, N0, N1, MODE>` (a wavefront per token) / `qkn_wide<Fmt, N0, N1, MODE>`, "
              "N0/N1 = 16-byte chunks per lane of the two tensors, MODE 0 fused, 1 apply (Phases B+C), "
              "2 Phase A, 3 fused with wait, 4 publish; SCHED 1 = pipelined.", "",
              "Runs of at least 20 consecutive dispatches of one kernel and shape, in order:", ""]
@@ -797,7 +805,7 @@ def summarize_proj(outdir: str) -> None:
         for r in csv.DictReader(open(os.path.join(path, files[0]))):
             name = r["Kernel_Name"]
             if "qkn_proj_gemm" in name:
-                key = "qkn_proj_gemm_dl (this library)"
+                key = f"{kernel_base_name(name)} (this library)"
             elif name.startswith("Cijk"):
                 key = "hipBLASLt GEMM (torch.mm)"
             else:

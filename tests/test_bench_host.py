@@ -3,6 +3,8 @@
 summaries rely on, and the counter file's source check."""
 import os
 
+import pytest
+
 import bench
 import workloads
 
@@ -59,3 +61,31 @@ def test_every_launch_name_family_maps():
         except ValueError:
             continue
         raise AssertionError(bad)
+
+
+def test_profiler_names_as_the_kernels_are_declared():
+    """qkn_rows has a last template argument (rows of any alignment); launches of a wavefront per token run
+    qkn_rows_once under the register path's launch name; each projection kernel keeps its own name."""
+    base = bench.kernel_base_name
+    rows = "void qkn_dev::qkn_rows<qkn_dev::FmtBf16, 4, 1, 0, 0, %s>(qkn_dev::KParams)"
+    assert base(rows % "false") == bench.trace_name("rows<4,1>/fused")
+    assert base(rows % "true") == "void qkn_rows<FmtBf16, 4, 1, 0, 0, true>"
+    assert base("void qkn_dev::qkn_rows_once<qkn_dev::FmtFp8, 2, 1, 1>(qkn_dev::KParams)") == \
+        bench.trace_name("rows_fp8<2,1>/apply", loop=False)
+    for name in ("rows_pf<2,1>/fused", "wide<16,1>/apply", "rows<2,0>/publish"):
+        with pytest.raises(ValueError):
+            bench.trace_name(name, loop=False)
+
+
+def test_projection_counters_stand_under_the_kernel_that_ran(tmp_path, monkeypatch):
+    for i, (sub, _) in enumerate(bench.PROJ_COUNTERS):
+        os.makedirs(tmp_path / sub)
+        (tmp_path / sub / "p_counter_collection.csv").write_text(
+            "Kernel_Name,Counter_Name,Counter_Value\n"
+            f"(anonymous namespace)::qkn_proj_gemm_big((anonymous namespace)::ProjParams),C{i},5\n"
+            f"Cijk_Alik_x,C{i},7\n")
+    os.makedirs(tmp_path / "profiles")
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    bench.summarize_proj(str(tmp_path))
+    text = next((tmp_path / "profiles").iterdir()).read_text()
+    assert "qkn_proj_gemm_big (this library):" in text and "qkn_proj_gemm_dl" not in text
