@@ -4,7 +4,8 @@ Widths, strides and addresses that 16-byte vectors do not divide, at the edges
 of a lane's 16 bytes, of a wavefront's 64 chunks and of the register path, as
 Q and K together: against the fp64 oracle, bit for bit against the staged
 general kernel (an independent implementation of the same arithmetic), with
-several tokens per wavefront, and with nothing written outside the rows.
+one token per wavefront and with several, and with nothing written outside the
+rows.
 """
 from __future__ import annotations
 
@@ -89,11 +90,12 @@ def test_any_rows(case):
     print(f"[any] {case}", flush=True)
     segs, bufs, two, info = fused([])
     again, _, _, info2 = fused([("force_generic", 1)])
-    few, _, _, _ = fused([("waves_per_cu", 1), ("balance", 1)])
+    one, _, _, info3 = fused([("waves_per_block", 1)])
     name = "generic_fp8/fused" if fp8 else "generic/fused"
     assert info["kernel"] == info2["kernel"] == name
+    assert info["waves"] == info3["waves"] == T  # a token per wavefront: the loops are in the tests below
     assert info["lds_bytes"] == 0 and info2["lds_bytes"] > 0  # registers; staged in LDS
-    for s, s2, s3, (P, y2), buf, ref, (_, _, d) in zip(segs, again, few, two, bufs, refs, data):
+    for s, s2, s3, (P, y2), buf, ref, (_, _, d) in zip(segs, again, one, two, bufs, refs, data):
         y = bits_of(s.y)
         if fp8:
             compare.check_fp8(Q.decode_e4m3(y), ref["y"], "y")
@@ -120,3 +122,99 @@ def test_any_rows_in_place():
     L.qkn_full([L.Seg(x=a, w=to_dev_f32(g), d_full=d, y=a)], 1e-6)
     torch.cuda.synchronize()
     assert np.array_equal(bits_of(a), bits_of(base))
+
+
+LOOPS = [  # (dtype, tokens, Q width, K width, options, threads per workgroup, tokens per wavefront at least)
+    ("bf16", 2049, 1100, 100, (("waves_per_cu", 1),), 64, 8),
+    ("bf16", 2049, 511, 2049, (("waves_per_cu", 1), ("balance", 1)), 64, 8),
+    ("fp8", 2049, 1025, 1000, (("waves_per_cu", 1),), 64, 8),
+    ("fp8", 2050, 33, 4095, (("waves_per_cu", 1), ("token_blocks", 1)), 64, 8),
+    # the default launch of many tokens: workgroups of four wavefronts, a last one that is not full
+    ("bf16", 8197, 1100, 100, (), 256, 2),
+    ("bf16", 6145, 1023, 515, (), 256, 3),
+    ("fp8", 8197, 2047, 100, (), 256, 2),
+    ("fp8", 20003, 1025, 31, (("token_blocks", 1),), 256, 2),
+]
+
+
+@pytest.mark.parametrize("case", LOOPS, ids=lambda c: "-".join(map(str, c[:4])) + "".join(k[0][0] for k in c[4]))
+def test_any_rows_loop(case):
+    """Several tokens per wavefront: the later ones go through the registers of the first. Fused, Phase A and
+    apply, with rows at every alignment (odd strides), bit for bit against the staged kernel."""
+    dtype, T, dq, dk, options, block, tokens = case
+    fp8, tp, rank, eps = dtype == "fp8", 3, 2, 1e-6
+    g = torch.Generator(device=DEV).manual_seed(T + dq)
+    elem = torch.float8_e4m3fn if fp8 else torch.bfloat16
+    data = []
+    for d in (dq, dk):
+        x = torch.randn(T, d + 1 + d % 2, device=DEV, generator=g).to(elem)
+        P = d * (0.5 + torch.rand(tp, T, device=DEV, generator=g))
+        data.append((x[:, 1:1 + d], torch.rand(d, device=DEV, generator=g) + 0.5, P))
+
+    def run(options):
+        for k, v in options:
+            L.qkn_set_option(k, v)
+        try:
+            segs, bufs, parts, info = [], [], [], []
+            for x, w, P in data:
+                P = P.clone()
+                y = torch.full((T, x.shape[1] + 3), 1, dtype=torch.uint8 if fp8 else torch.int16, device=DEV)
+                segs.append(L.Seg(x=x, w=w, d_full=x.shape[1] * tp, y=y.view(elem)[:, 2:2 + x.shape[1]], partials=P,
+                                  inv_rms=torch.empty(T, device=DEV)))
+                bufs.append(y)
+            (L.qkn_fused_shard_fp8 if fp8 else L.qkn_fused_shard)(segs, tp, rank, eps)
+            info.append(L.qkn_last_launch())
+            for s in segs:
+                P = s.partials.clone()
+                P[rank] = 0
+                (L.qkn_partial_sumsq_fp8 if fp8 else L.qkn_partial_sumsq)(s.x, out=P[rank])
+                info.append(L.qkn_last_launch())
+                parts.append((P, (L.qkn_apply_fp8 if fp8 else L.qkn_apply)(s.x, s.w, P, s.d_full, eps)))
+                info.append(L.qkn_last_launch())
+        finally:
+            for k, _ in options:
+                L.qkn_set_option(k, 0)
+        torch.cuda.synchronize()
+        return segs, bufs, parts, info
+
+    print(f"[any loop] {case}", flush=True)
+    segs, bufs, parts, info = run(options)
+    want, _, wparts, _ = run([("force_generic", 1)])
+    assert info[0]["block"] == block and info[0]["lds_bytes"] == 0, info[0]
+    assert info[0]["waves"] * tokens <= T + 3 and all(i["block"] == block for i in info), info
+    for s, whole, w, (P, y), (wP, wy) in zip(segs, bufs, want, parts, wparts):
+        assert np.array_equal(bits_of(s.y), bits_of(w.y)) and torch.equal(s.partials, w.partials)
+        assert torch.equal(s.inv_rms, w.inv_rms) and torch.equal(P, wP)
+        assert np.array_equal(bits_of(y), bits_of(wy)) and np.array_equal(bits_of(y), bits_of(s.y))
+        assert bool((whole[:, :2] == 1).all()) and bool((whole[:, -1] == 1).all())
+    for s in segs:  # and the staged kernel is right: the statistic and the products in fp64
+        x = s.x.float().double()
+        S = x.square().sum(1)
+        compare.check_close(s.partials[rank].cpu().numpy(), S.cpu().numpy(), compare.PARTIAL_RTOL, "own partial")
+        inv = (s.partials.double().sum(0) / s.d_full + eps).rsqrt()
+        y = (x * s.w.double() * inv[:, None]).cpu().numpy()
+        if fp8:
+            compare.check_fp8(Q.decode_e4m3(bits_of(s.y)), y, "y")
+        else:
+            compare.check_close(Q.decode_bf16(bits_of(s.y)), y, compare.OUTPUT_RTOL, "y")
+
+
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+@pytest.mark.parametrize("T,d", [(40, 515), (40, 1100), (2049, 1100)])
+def test_any_apply_in_place(T, d, fp8):
+    """No Phase A sum stands between a row's loads and its stores: the last chunk, fetched as the row's last 16
+    bytes, overlaps what the chunk before it stores."""
+    g = torch.Generator(device=DEV).manual_seed(d)
+    x = torch.randn(T, d, device=DEV, generator=g).to(torch.float8_e4m3fn if fp8 else torch.bfloat16)
+    w = torch.rand(d, device=DEV, generator=g) + 0.5
+    P = d * (0.5 + torch.rand(2, T, device=DEV, generator=g))
+    apply = L.qkn_apply_fp8 if fp8 else L.qkn_apply
+    want = apply(x, w, P, 2 * d, 1e-6)
+    L.qkn_set_option("waves_per_cu", 1)
+    try:
+        got = apply(x, w, P, 2 * d, 1e-6, y=x)
+        info = L.qkn_last_launch()
+    finally:
+        L.qkn_set_option("waves_per_cu", 0)
+    assert info["kernel"].startswith("generic") and (T < 2049 or info["waves"] * 8 <= T)
+    assert np.array_equal(bits_of(got), bits_of(want))
