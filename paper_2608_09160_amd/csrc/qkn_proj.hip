@@ -1096,14 +1096,14 @@ __global__ __launch_bounds__(kBigThreads, 2) void qkn_proj_gemm_big(const ProjPa
 }
 
 // The segment, origin and valid extent of output tile (row tile mt of height
-// 64 WMB from row `row0`, column tile nt over both segments).
+// 64 WMB, column tile nt over both segments).
 struct TileAt {
   int si;
   int64_t m0;
   int n0, rows_a, rows_b;
 };
 template <int WMB>
-__device__ __forceinline__ TileAt tile_at(const ProjParams& p, int64_t row0, int mt, int nt) {
+__device__ __forceinline__ TileAt tile_at(const ProjParams& p, int mt, int nt) {
   // The tile numbers are uniform, but the integer divisions that produced
   // them run on the vector unit; without this the compiler can treat the
   // buffer descriptors built from them as per-lane values and wrap every
@@ -1113,7 +1113,7 @@ __device__ __forceinline__ TileAt tile_at(const ProjParams& p, int64_t row0, int
   TileAt t;
   t.si = (p.nseg == 2 && nt >= p.seg[1].tile0) ? 1 : 0;
   const ProjSegDev& s = p.seg[t.si];
-  t.m0 = row0 + static_cast<int64_t>(mt) * (64 * WMB);
+  t.m0 = static_cast<int64_t>(mt) * (64 * WMB);
   t.n0 = (nt - s.tile0) * 128;
   t.rows_a = static_cast<int>((p.T - t.m0 < 64 * WMB) ? p.T - t.m0 : 64 * WMB);
   t.rows_b = (s.d - t.n0 < 128) ? s.d - t.n0 : 128;
@@ -1122,9 +1122,8 @@ __device__ __forceinline__ TileAt tile_at(const ProjParams& p, int64_t row0, int
 
 // One whole tile with its epilogue.
 template <int MI, int WMB, int BK, int S>
-__device__ __forceinline__ void dl_tile(const ProjParams& p, unsigned char* lds, int64_t row0,
-                                        int mt, int nt) {
-  const TileAt t = tile_at<WMB>(p, row0, mt, nt);
+__device__ __forceinline__ void dl_tile(const ProjParams& p, unsigned char* lds, int mt, int nt) {
+  const TileAt t = tile_at<WMB>(p, mt, nt);
   const ProjSegDev& s = p.seg[t.si];
   typename AccOf<MI, WMB>::T acc;
   dl_mainloop<MI, WMB, BK, S>(p, s, lds, t.m0, t.n0, t.rows_a, t.rows_b, 0, p.hidden, acc);
@@ -1144,7 +1143,7 @@ __global__ __launch_bounds__(kThreads) void qkn_proj_gemm_dl(const ProjParams p)
   int mt, nt;
   if (!tile_of(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x), p.m_tiles, p, mt, nt))
     return;
-  dl_tile<MI, 2, BK, S>(p, lds, 0, mt, nt);
+  dl_tile<MI, 2, BK, S>(p, lds, mt, nt);
 }
 
 constexpr int kSplitBk = 64;
@@ -1234,8 +1233,8 @@ __global__ __launch_bounds__(kBigThreads, S == 2 ? 4 : 2) void qkn_proj_gemm_spl
 }
 
 // Split k, up to 64 tokens and one workgroup per CU: workgroup b takes k-slice
-// b mod splits of the 64-row tile b / splits and stores its fp32 sums into the slice array instead of
-// running the epilogue.
+// b mod splits of the 64-row tile b / splits and stores its fp32 sums into the
+// slice array instead of running the epilogue.
 __global__ __launch_bounds__(kThreads) void qkn_proj_gemm_decode(const ProjParams p) {
   constexpr int WMB = 1, BK = kSplitBk, S = kSplitStages;
   constexpr int MI = 16;  // 16 x 16 x 32 MFMAs (same bits as 32 x 32 x 16, 1-2 % faster here)
@@ -1259,8 +1258,8 @@ __global__ __launch_bounds__(kThreads) void qkn_proj_gemm_decode(const ProjParam
   using A = AccOf<MI, WMB>;
   typename A::T acc;
   dl_mainloop<MI, WMB, BK, S>(p, s, lds, t.m0, t.n0, t.rows_a, t.rows_b, k_lo, k_hi, acc);
-  // fp32 sums of this k-slice, through LDS: the accumulators (lanes 0..MI-1
-  // of a row hold MI adjacent columns) go to an fp32 tile in LDS, which is
+  // fp32 sums of this k-slice, through LDS: the accumulators (sixteen lanes
+  // hold a row's adjacent columns) go to an fp32 tile in LDS, which is
   // then written out row by row in 16-byte vectors (4-byte stores straight
   // from the accumulators scatter every wave instruction over 4 rows).
   const int tid = static_cast<int>(threadIdx.x);
@@ -1276,12 +1275,10 @@ __global__ __launch_bounds__(kThreads) void qkn_proj_gemm_decode(const ProjParam
   for (int i = 0; i < A::kM; ++i)
 #pragma unroll
     for (int j = 0; j < A::kN; ++j) {
-      const int col = wn * 64 + j * MI + (lane & (MI - 1));
+      const int col = wn * 64 + j * 16 + (lane & 15);
 #pragma unroll
       for (int r = 0; r < A::kR; ++r) {
-        const int row = (MI == 32)
-            ? wm * 32 * WMB + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)
-            : wm * 32 * WMB + i * 16 + 4 * (lane >> 4) + r;
+        const int row = wm * 32 * WMB + i * 16 + 4 * (lane >> 4) + r;
         tile[row * kRow + col] = acc[i][j][r];
       }
     }
