@@ -72,6 +72,14 @@ def parse():
                    help="write profiles/counters_*.txt and profiles/issue_rate_*.md from the "
                         "rocprofv3 --pmc output of `bench.py --counter-pass` in DIR/<pass> "
                         "(one directory per entry of COUNTER_PASSES) and DIR/counter_pass.json")
+    p.add_argument("--case-pass", action="store_true",
+                   help="run every listed case of perf/cases.py a fixed number of times between "
+                        "marker launches and print their list as JSON: the program profiled for "
+                        "profiles/cases.md")
+    p.add_argument("--summarize-cases", metavar="DIR",
+                   help="write profiles/cases.md from the rocprofv3 output of `bench.py --case-pass` "
+                        "(a kernel trace in DIR/trace, counters in DIR/<pass> per entry of "
+                        "CASE_PASSES) and DIR/case_pass.json")
     p.add_argument("--calibration-copy", action="store_true",
                    help="also run a plain device copy of Q's input (known bytes) a few times, "
                         "to scale profiler byte counters")
@@ -828,6 +836,106 @@ def summarize_proj(outdir: str) -> None:
     print("\n".join(lines))
 
 
+CASE_PASSES = COUNTER_PASSES[:2] + PROJ_COUNTERS
+CASE_STEPS = 10
+
+
+def case_pass(torch, L) -> list:
+    """CASE_STEPS passes of every listed case (the calls of a graph one by one)
+    between marker launches, after a device copy of known bytes."""
+    from perf import cases
+    a = torch.empty(32 << 20, dtype=torch.uint8, device="cuda:0")
+    b = torch.empty_like(a)
+    out = []
+
+    def run(name, work, step):
+        for _ in range(3):
+            step()
+        torch.cuda.synchronize()
+        L.qkn_calib_empty()
+        for _ in range(CASE_STEPS):
+            step()
+        L.qkn_calib_empty()
+        torch.cuda.synchronize()
+        out.append({"name": name, **work})
+        print(f"[cases] {name}", file=sys.stderr, flush=True)
+
+    run("copy", {"bytes": 2 * a.numel(), "flops": 0}, lambda: b.copy_(a))
+    for case in cases.listed():
+        state = cases.prepare(case, 1)
+        if case["kind"] == "layers":
+            run(case["name"], cases.work(case), lambda: [call() for block in state["blocks"] for call in block])
+        else:
+            run(case["name"], cases.work(case), lambda: cases.run(state))
+        del state
+    return out
+
+
+def summarize_cases(outdir: str) -> None:
+    """profiles/cases.md: every kernel of every listed case, its time and counters per dispatch."""
+    import csv
+    import glob
+    cases = json.loads(open(os.path.join(outdir, "case_pass.json")).read().strip().splitlines()[-1])
+    trace = glob.glob(os.path.join(outdir, "trace", "**", "*_kernel_trace.csv"), recursive=True)[0]
+    rows = sorted(csv.DictReader(open(trace)), key=lambda r: int(r["Start_Timestamp"]))
+    times = _split_cases([(kernel_base_name(r["Kernel_Name"]),
+                           {"us": (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3}) for r in rows],
+                         len(cases))
+    segs = {tag: _split_cases(_counter_rows(os.path.join(outdir, tag)), len(cases)) for tag, _ in CASE_PASSES}
+    half = cases[0]["bytes"] / 2 / 1024
+    scale = {c: half / sum(m for _, m, _ in _per_kernel_means(segs[tag][0], c))
+             for tag, c in CASE_PASSES[:2]}
+    names = [c for _, cs in CASE_PASSES[2:] for c in cs.split()]
+    lines = ["# Kernels of the listed performance cases", "",
+             f"Source sha256: norms {source_sha256()}, projection {proj_sha256()}. Commands (MI355X, repository "
+             "root):", "",
+             "    python -u bench.py --case-pass > gpurun_out/cases/case_pass.json",
+             "    rocprofv3 --kernel-trace --output-format csv -d gpurun_out/cases/trace -o c -- "
+             "python -u bench.py --case-pass"] + \
+            [f"    rocprofv3 --pmc {cs} --output-format csv -d gpurun_out/cases/{tag} -o c -- "
+             "python -u bench.py --case-pass" for tag, cs in CASE_PASSES] + \
+            ["    python bench.py --summarize-cases gpurun_out/cases", "",
+             f"{CASE_STEPS} passes of each case, the calls of a graph launched one by one. Per dispatch: median time "
+             "in the kernel trace; megabytes that the L2s fetched and wrote (FETCH_SIZE and WRITE_SIZE, scaled by "
+             f"{scale['FETCH_SIZE']:.3f} and {scale['WRITE_SIZE']:.3f}, which make a copy of 32 MiB come out right; "
+             "the last-level cache serves part of them); shares of the time: MFMA = SQ_VALU_MFMA_BUSY_CYCLES over the cycles of 1024 SIMDs, LDS = the time that "
+             "SQ_INSTS_LDS instructions of 1 KB need at 128 bytes per cycle and CU (an upper bound where "
+             "instructions move less; loads straight into LDS are not counted), conflicts = SQ_LDS_BANK_CONFLICT "
+             "over the cycles of 256 CUs, waiting = SQ_WAIT_ANY / SQ_WAVE_CYCLES. Cycles from GRBM_GUI_ACTIVE / 8 of "
+             "the counter run.", "",
+             "| case | kernel | per pass | us | MB read | MB written | waves | MFMA | LDS | conflicts | waiting |",
+             "|---|---|---|---|---|---|---|---|---|---|---|"]
+    for i, c in enumerate(cases):
+        if i == 0:
+            continue
+        per = {}
+        for tag, cs in CASE_PASSES:
+            for counter in cs.split():
+                for n, m, _ in _per_kernel_means(segs[tag][i], counter):
+                    per.setdefault(n, {})[counter] = m
+        order = []
+        for n, _ in times[i]:
+            if n not in order:
+                order.append(n)
+        for n in order:
+            us = [v["us"] for k, v in times[i] if k == n]
+            v = per.get(n, {})
+            cyc = v.get("GRBM_GUI_ACTIVE", 0) / 8
+            mb = [f"{v[x] * scale[x] * 1024 / 1e6:.2f}" if x in v else "-" for x in ("FETCH_SIZE", "WRITE_SIZE")]
+            share = ["-"] * 4
+            if cyc and all(x in v for x in names):
+                share = [f"{v['SQ_VALU_MFMA_BUSY_CYCLES'] / (1024 * cyc):.2f}",
+                         f"{v['SQ_INSTS_LDS'] * 1024 / (256 * 128 * cyc):.2f}",
+                         f"{v['SQ_LDS_BANK_CONFLICT'] / (256 * cyc):.3f}",
+                         f"{v['SQ_WAIT_ANY'] / v['SQ_WAVE_CYCLES']:.2f}"]
+            lines.append(f"| {c['name']} | `{n}` | {len(us) / CASE_STEPS:g} | {float(np.median(us)):.2f} | "
+                         f"{mb[0]} | {mb[1]} | {v.get('SQ_WAVES', 0):.0f} | " + " | ".join(share) + " |")
+    path = os.path.join(ROOT, "profiles", "cases.md")
+    with open(path, "w") as f:
+        f.write("\n".join(lines) + "\n")
+    print("\n".join(lines[lines.index(next(x for x in lines if x.startswith("| case"))):]))
+
+
 def cpu_baseline(wl, rank, data, seconds):
     """The fp64 oracle as it stands, on the host: bounded sample of the workload."""
     from oracle import qknorm as Q
@@ -878,6 +986,9 @@ def main():
     if args.summarize_counters:
         summarize_counters(args.summarize_counters)
         return 0
+    if args.summarize_cases:
+        summarize_cases(args.summarize_cases)
+        return 0
     world = int(os.environ.get("WORLD_SIZE", "1"))
     if args.gpus != 1 or world != 1:
         print("bench.py measures one GPU's share of the sharded QK-Norm; the peer ranks "
@@ -896,6 +1007,9 @@ def main():
     if args.proj_only:
         out = {"proj_partial_prefill": proj_extra(torch, L, workloads, wl, args.rank, steps=10)}
         print(json.dumps(out), flush=True)
+        return 0
+    if args.case_pass:
+        print(json.dumps(case_pass(torch, L)), flush=True)
         return 0
     if args.counter_pass:
         print(json.dumps(counter_pass(torch, L, workloads, args.min_footprint_mb << 20)), flush=True)

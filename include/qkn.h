@@ -336,8 +336,10 @@ int qkn_last_launch(qkn_launch_info* info);
  *                    number of tokens, 0 = use the full grid (default);
  *   "token_blocks"   1 = each wavefront takes a contiguous range of tokens,
  *                    0 = tokens strided by the wavefront count (default);
- *   "waves_per_block" 1..4, 0 = automatic (register path: 1 for bf16,
- *                    4 for fp8 and for rows of any alignment; wide path:
+ *   "waves_per_block" 1..4, 0 = automatic (register path: 1, but 4 from 24
+ *                    tokens per CU for fp8 and for rows of any alignment, and
+ *                    from 32 tokens per CU for bf16 launches of one phase,
+ *                    apply or Phase A alone, of up to 3072 columns; wide path:
  *                    always 4);
  *   "force_generic"  1 = always take the general path's staged kernel (same
  *                    results);

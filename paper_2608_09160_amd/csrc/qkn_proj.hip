@@ -696,12 +696,14 @@ __device__ __forceinline__ void dl_mainloop(const ProjParams& p, const ProjSegDe
 //     the epilogue instead of 2-byte ones. Every output still takes k in
 //     ascending blocks of 32: the bits are those of the 128 x 128 kernel.
 // Measured (8192 tokens, hidden 4096): 2048 columns, 256 tiles: 110 us against
-// 144; 2048 + 512 columns: 157 us against 205; from 4096 to 8192 hidden the
-// time grows at 1.40 PF/s (the library GEMM: 1.56). Without its loads the same
-// loop runs at 1.55 PF/s and with every load an L2 hit at 1.45: the LDS write
-// port and L2 set the rest. Four wavefronts of 128 x 128 (one per SIMD, so
-// nothing covers a wait) took 155-160 us, loads spread between the LDS reads
-// and raised wave priorities changed nothing.
+// 144; a call of 2048 + 512 columns, quarters on the role-split loop: 140-144
+// us against 199; from 4096 to 8192 hidden the time grows at 1.40 PF/s (the
+// library GEMM: 1.56). Without its loads the same loop runs at 1.55 PF/s and
+// with every load an L2 hit at 1.45. Counters of that call: the matrix cores
+// are busy 60 % of the cycles, LDS moves data 67 % of them (reads 50, fills
+// 17), and the L2s fetch 386 MB for operands of 88. Four wavefronts of 128 x
+// 128 (one per SIMD, so nothing covers a wait) took 155-160 us, loads spread
+// between the LDS reads and raised wave priorities changed nothing.
 template <int TM, int TN>
 struct BigCfg {
   static constexpr int S = 2;                                // LDS stages
@@ -1173,10 +1175,11 @@ struct SplitCfg {
 // role-split loop on four stages, or the eight-wavefront one on two (two or
 // three workgroups per CU), and stores its fp32 sums into the slice array
 // instead of running the epilogue. Bound by LDS like the small whole tiles
-// (0.32 us per stage of 64 k) plus 6 us of first loads, stores and launch.
-// Before, four wavefronts of 64 x 64 without fragments ahead, and with each
-// XCD's workgroups spread over all tiles so that every XCD's L2 fetched nearly
-// all of x and W: 512 tokens, hidden 4096, 1536 columns 22.4 -> 17.5 us a call.
+// (0.32 us per stage of 64 k, in which LDS moves 96 KB at 128 bytes per cycle)
+// plus 6 us of first loads, stores and launch. Before, four wavefronts of 64 x
+// 64 without fragments ahead, and with each XCD's workgroups spread over all
+// tiles: 512 tokens, hidden 4096, 1536 columns 22.4 -> 17.5 us a call; at 777
+// tokens, hidden 5120, the L2s fetched 95 MB for 24 MB of x and W, now 48.
 template <int TM, int S>
 __global__ __launch_bounds__(kBigThreads, S == 2 ? 4 : 2) void qkn_proj_gemm_split(const ProjParams p) {
   constexpr bool kDuo = S == 4;
@@ -1564,7 +1567,7 @@ Plan plan_of(int64_t T, int64_t hidden, const qkn_proj_seg* segs, int nseg) {
 // of a microsecond: 256 x 256 tiles (one per CU), 128 x 128 tiles of the
 // large-tile kernel (one per CU), 128 x 128 tiles of the two-stage kernel (two
 // per CU). Fitted to whole calls at 1025 to 12000 tokens, 640 to 5120 columns,
-// hidden 1024 and 4096. So up to 256 small tiles take the role-split loop
+// hidden 1024 and 4096, repeated on the same operands. So up to 256 small tiles take the role-split loop
 // (1536 tokens x 1280 columns, hidden 4096: 28.8 against 51.2 us), 257 to 512
 // take it from hidden 3072 or so (4096 tokens x 1536 columns: hidden 4096 55.3
 // against 60.0 us, hidden 1024 24.5 against 24.1), and larger launches take
