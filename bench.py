@@ -476,11 +476,11 @@ def summarize(outdir: str) -> None:
             plain = [f"The untraced `python bench.py` run of the same session: kernel_us {k_us} "
                      f"(timed region / launches), {abs(k_us - mean_us) / mean_us:.1%} from the "
                      f"trace's mean; value {pb['value']} GB/s, roofline.frac {pb['roofline']['frac']}."]
-    cmd_trace = ("rocprofv3 --kernel-trace --stats --output-format csv -d gpurun_out/trace -o bench "
-                 "-- python -u bench.py --no-cpu-baseline > gpurun_out/trace_bench.json")
+    cmd_trace = ("rocprofv3 --kernel-trace --stats --output-format csv -d out/trace -o bench "
+                 "-- python -u bench.py --no-cpu-baseline > out/trace_bench.json")
     lines = [f"# Kernel trace: {kernel} on {workload}", "",
              f"Kernel source sha256 {sha}. Commands (MI355X, repository root):", "",
-             f"    {cmd_trace}", "    python bench.py --summarize gpurun_out", "",
+             f"    {cmd_trace}", "    python bench.py --summarize out", "",
              f"Headline kernel `{tname}` (launch name `{kernel}`), the run of {len(headline)} "
              f"consecutive dispatches of the bench's timed and per-launch passes: mean "
              f"{mean_us:.3f} us -> {algo} algorithmic bytes / {mean_us:.3f} us = "
@@ -657,10 +657,10 @@ def summarize_counters(outdir: str) -> None:
     half = cases[cal]["bytes_per_step"] // 2
     sf, sw = half / 1024 / cal_f, half / 1024 / cal_w
     sha, psha = source_sha256(), proj_sha256()
-    cmds = ["python -u bench.py --counter-pass > gpurun_out/counters/counter_pass.json"] + [
-        f"rocprofv3 --pmc {ctrs} --output-format csv -d gpurun_out/counters/{tag} -o c -- "
+    cmds = ["python -u bench.py --counter-pass > out/counters/counter_pass.json"] + [
+        f"rocprofv3 --pmc {ctrs} --output-format csv -d out/counters/{tag} -o c -- "
         f"python -u bench.py --counter-pass" for tag, ctrs in COUNTER_PASSES] + [
-        "python bench.py --summarize-counters gpurun_out/counters"]
+        "python bench.py --summarize-counters out/counters"]
     written = []
     for i, c in enumerate(cases):
         if i == cal:
@@ -808,7 +808,7 @@ def summarize_proj(outdir: str) -> None:
         files = [f for f in os.listdir(path) if f.endswith("counter_collection.csv")]
         if not files:
             raise SystemExit(f"no counter CSV in {path}")
-        cmds.append(f"rocprofv3 --pmc {counters} --output-format csv -d gpurun_out/{sub} -o p "
+        cmds.append(f"rocprofv3 --pmc {counters} --output-format csv -d out/{sub} -o p "
                     "-- python -u bench.py --proj-only")
         for r in csv.DictReader(open(os.path.join(path, files[0]))):
             name = r["Kernel_Name"]
@@ -823,7 +823,7 @@ def summarize_proj(outdir: str) -> None:
              f"source_sha256 (qkn_proj.hip): {proj_sha256()}",
              "commands (on the MI355X, from the repository root):"]
     lines += ["  " + c for c in cmds]
-    lines += ["  python bench.py --summarize-proj gpurun_out",
+    lines += ["  python bench.py --summarize-proj out",
               "mean counter value per dispatch (sums over the GPU):"]
     for key in sorted(rows):
         lines.append(key + ":")
@@ -889,12 +889,12 @@ def summarize_cases(outdir: str) -> None:
     lines = ["# Kernels of the listed performance cases", "",
              f"Source sha256: norms {source_sha256()}, projection {proj_sha256()}. Commands (MI355X, repository "
              "root):", "",
-             "    python -u bench.py --case-pass > gpurun_out/cases/case_pass.json",
-             "    rocprofv3 --kernel-trace --output-format csv -d gpurun_out/cases/trace -o c -- "
+             "    python -u bench.py --case-pass > out/cases/case_pass.json",
+             "    rocprofv3 --kernel-trace --output-format csv -d out/cases/trace -o c -- "
              "python -u bench.py --case-pass"] + \
-            [f"    rocprofv3 --pmc {cs} --output-format csv -d gpurun_out/cases/{tag} -o c -- "
+            [f"    rocprofv3 --pmc {cs} --output-format csv -d out/cases/{tag} -o c -- "
              "python -u bench.py --case-pass" for tag, cs in CASE_PASSES] + \
-            ["    python bench.py --summarize-cases gpurun_out/cases", "",
+            ["    python bench.py --summarize-cases out/cases", "",
              f"{CASE_STEPS} passes of each case, the calls of a graph launched one by one. Per dispatch: median time "
              "in the kernel trace; megabytes that the L2s fetched and wrote (FETCH_SIZE and WRITE_SIZE, scaled by "
              f"{scale['FETCH_SIZE']:.3f} and {scale['WRITE_SIZE']:.3f}, which make a copy of 32 MiB come out right; "
